@@ -277,9 +277,9 @@ int varlen_attn_bwd(const void* q, const void* k, const void* v, const void* out
  * becomes the NaN code 0x7F at its own place and stays out of the maximum, and
  * an infinity makes the descale of its head infinite):
  *   x        device in   bfloat16 [T, H, D], 16-byte aligned, D a multiple of 8
- *   codes    device out  uint8 [T, H, D], 8-byte aligned
- *   descale  device out  float32 [H]; holds the per-head maxima while the call runs
- * Four small kernels on `stream`; nothing is allocated, nothing waits.
+ *   codes    device out  uint8 [T, H, D], 8-byte aligned; holds maxima of parts of x while the call runs
+ *   descale  device out  float32 [H]
+ * Two kernels on `stream`; nothing is allocated, nothing waits.
  * VA_EINVAL for null pointers or bad sizes, VA_EALIGN, VA_EHIP.
  */
 int va_quantize_e4m3_per_head_device(const void* x_bf16, int32_t T, int32_t H, int32_t D,

@@ -4,11 +4,11 @@
 // saturating at +-448.  (The scaling vocabulary is that of section 2.2.3;
 // applying it per attention head is this library's choice.)
 //
-// Four small kernels on the caller's stream: clear the per-head maxima, reduce
-// |x| per head, encode, turn the maxima into descales.  The descale array holds
-// the maxima (as float bits: for non-negative floats the integer order is the
-// float order) until the last kernel; nothing else is needed, nothing is
-// allocated.
+// Two kernels on the caller's stream, no atomics on global memory and nothing to clear.  The rows are cut into
+// R runs, one workgroup each.  The first kernel takes the per-head maxima of its run and leaves them in the
+// code array, which nobody needs before the codes are written: once in the part of every one of the R
+// workgroups.  In the second kernel a workgroup reads the R maxima of each head from its own part, and only
+// then overwrites that part with codes, so no workgroup depends on another of the same launch.
 //
 // The block-wise quantiser (one scale per 128 tokens of one sample and one
 // head, bit-identical to va_quantize_e4m3_blockwise) is one kernel further down.
@@ -18,13 +18,6 @@
 namespace va {
 
 namespace {
-
-constexpr int kMaxHeadsInLds = 256;
-
-__global__ void quant_clear_kernel(unsigned* amax_bits, int H) {
-    const int h = blockIdx.x * blockDim.x + threadIdx.x;
-    if (h < H) amax_bits[h] = 0u;
-}
 
 VA_DEV float bf16_bits_to_float(unsigned bits16) { return __builtin_bit_cast(float, bits16 << 16); }
 
@@ -50,72 +43,154 @@ VA_DEV float descale_of(unsigned amax_bits) {
     return s > 0.0f ? s : 1.0f;
 }
 
-// Eight bf16 values -> eight E4M3 codes of value / descale.
-VA_DEV i32x2 encode_chunk(u32x4 raw, float descale) {
+// A head's or block's descale with what the encoder needs beside it.
+struct Scale {
+    float d, r;    // descale and its reciprocal, both rounded once
+    bool by_mult;  // d so far from the ends of the float32 range that no step of encode_chunk leaves the normal numbers
+    VA_DEV explicit Scale(float descale) : d(descale), r(1.0f / descale), by_mult(descale > 0x1p-80f && descale < 0x1p120f) {}
+};
+
+// Eight bf16 values -> eight E4M3 codes of value / descale.  The quotient is the correctly rounded one in both
+// branches: x * r is corrected once by its remainder.  (Both mantissas come from 8-bit numbers, so that was
+// checked for every pair: the corrected product equals the division bit for bit, where x * r alone gives another
+// code for some pairs on a rounding boundary.  The remainder is formed negated, q * d - x, which keeps the sign
+// of a zero.)  A division is some ten instructions per value, and they, not memory, set the pace of these
+// kernels.  |x| <= amax, so |quotient| rounds to at most 448 and needs no clamp.
+VA_DEV i32x2 encode_chunk(u32x4 raw, const Scale& s) {
     float v[8];
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
-        v[2 * w] = bf16_bits_to_float(raw[w] & 0xffffu) / descale;
-        v[2 * w + 1] = bf16_bits_to_float(raw[w] >> 16) / descale;
+        v[2 * w] = bf16_bits_to_float(raw[w] & 0xffffu);
+        v[2 * w + 1] = __builtin_bit_cast(float, raw[w] & 0xffff0000u);
     }
-    // The conversion instruction rounds to nearest even, subnormals included, but turns magnitudes of
-    // 464 and more into NaN instead of saturating: clamp first (448 is representable).  The clamp would
-    // also turn a NaN into -448; a NaN (the value itself, or infinity over an infinite scale) gets the
-    // NaN code 0x7F of the host routine instead.
-    unsigned nan_lo = 0u, nan_hi = 0u;
+    if (s.by_mult) {
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        if (v[e] != v[e]) (e < 4 ? nan_lo : nan_hi) |= 0xffu << (8 * (e & 3));
-        v[e] = fminf(fmaxf(v[e], -448.0f), 448.0f);
+        for (int e = 0; e < 8; ++e) {
+            const float q = v[e] * s.r;
+            v[e] = __builtin_fmaf(-__builtin_fmaf(q, s.d, -v[e]), s.r, q);
+        }
+    } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = v[e] / s.d;
     }
-    int lo = __builtin_amdgcn_cvt_pk_fp8_f32(v[0], v[1], 0, false);
-    lo = __builtin_amdgcn_cvt_pk_fp8_f32(v[2], v[3], lo, true);
-    int hi = __builtin_amdgcn_cvt_pk_fp8_f32(v[4], v[5], 0, false);
-    hi = __builtin_amdgcn_cvt_pk_fp8_f32(v[6], v[7], hi, true);
-    lo = (int)(((unsigned)lo & ~nan_lo) | (0x7f7f7f7fu & nan_lo));
-    hi = (int)(((unsigned)hi & ~nan_hi) | (0x7f7f7f7fu & nan_hi));
-    return i32x2{lo, hi};
+    // The conversion instruction rounds to nearest even, subnormals included.  A NaN (the value itself, or
+    // infinity over an infinite scale) becomes the NaN code with the sign it had: the host routine's is 0x7F,
+    // so the sign goes wherever the other seven bits are all ones.
+    i32x2 codes;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        int word;  // the half the first conversion leaves alone is overwritten by the second: any old value serves
+        asm volatile("" : "=v"(word));
+        word = __builtin_amdgcn_cvt_pk_fp8_f32(v[4 * i], v[4 * i + 1], word, false);
+        word = __builtin_amdgcn_cvt_pk_fp8_f32(v[4 * i + 2], v[4 * i + 3], word, true);
+        const unsigned nan = ((unsigned)word & 0x7f7f7f7fu) + 0x01010101u;
+        codes[i] = (int)((unsigned)word & ~(nan & 0x80808080u));
+    }
+    return codes;
 }
 
-// x is [rows = T * H, D] bf16; a thread takes 8 consecutive values (16 bytes) at a time.
-__global__ __launch_bounds__(256) void quant_amax_kernel(const uint16_t* x, size_t chunks, int chunks_per_row, int H,
-                                                         unsigned* amax_bits) {
-    __shared__ unsigned lds_max[kMaxHeadsInLds];
-    const bool use_lds = H <= kMaxHeadsInLds;
-    if (use_lds) {
-        for (int h = threadIdx.x; h < H; h += blockDim.x) lds_max[h] = 0u;
-        __syncthreads();
+// ---------------------------------------------------------------- per-head scales
+
+constexpr int kQuantThreads = 1024;
+constexpr int kQuantUnroll = 4;      // 16-byte loads a thread has in flight
+constexpr int kMaxRuns = 256;        // one workgroup per CU; every run leaves its maxima in every other's part
+constexpr int kHeadsPerGroup = 256;  // heads a workgroup handles (their maxima live in LDS)
+
+// The share of workgroup (run i, head group y): token rows [r0, r1), heads [h0, h0 + heads).  A thread
+// stays on one column of 8 values, hence on one head, and walks down the rows.
+struct QuantShare {
+    int r0, r1, h0, heads, columns, rows_at_once;
+    size_t row_chunks;  // chunks of 8 values from one token row to the next
+    VA_DEV QuantShare(int T, int H, int cpr, int runs) {
+        r0 = (int)((long long)blockIdx.x * T / runs);
+        r1 = (int)((long long)(blockIdx.x + 1) * T / runs);
+        h0 = (int)blockIdx.y * kHeadsPerGroup;
+        heads = min(H - h0, kHeadsPerGroup);
+        columns = heads * cpr;
+        rows_at_once = max(1, kQuantThreads / columns);
+        row_chunks = (size_t)H * cpr;
     }
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < chunks; i += (size_t)gridDim.x * blockDim.x) {
-        const u32x4 raw = *reinterpret_cast<const u32x4*>(x + i * 8);
-        const unsigned m = chunk_amax_bits(raw);
-        const int h = (int)((i / chunks_per_row) % H);
-        if (use_lds) atomicMax(&lds_max[h], m);
-        else atomicMax(&amax_bits[h], m);
+    // f(row, chunk column, row step) for the thread's share; threads past the last whole row stay idle
+    template <typename F>
+    VA_DEV void for_columns(F f) const {
+        if ((int)threadIdx.x >= columns * rows_at_once) return;
+        for (int c = (int)threadIdx.x % columns; c < columns; c += kQuantThreads)
+            f(r0 + (int)threadIdx.x / columns % rows_at_once, c, rows_at_once);
     }
-    if (use_lds) {
-        __syncthreads();
-        for (int h = threadIdx.x; h < H; h += blockDim.x)
-            if (lds_max[h] != 0u) atomicMax(&amax_bits[h], lds_max[h]);
+};
+
+// Where word k of the maxima left for run r, head group [h0, h0 + heads) lies in the code array: in the rows of
+// that run and the columns of those heads, row after row, so that only bytes the workgroup (r, y) will
+// write itself are used.  The host chooses the number of runs so that R * heads words fit.
+VA_DEV unsigned* partial_word(unsigned char* codes, int r, int k, int T, int H, int D, int runs, int h0, int heads) {
+    const int words_per_row = heads * D / 4;
+    const int row = (int)((long long)r * T / runs) + k / words_per_row;
+    return reinterpret_cast<unsigned*>(codes + ((size_t)row * H + h0) * D) + k % words_per_row;
+}
+
+// 67 MB (16384 tokens, 16 heads, D = 128): bound by the read.
+__global__ __launch_bounds__(kQuantThreads) void quant_partial_max_kernel(const u32x4* x, int T, int H, int D, int runs,
+                                                                         unsigned char* codes) {
+    __shared__ unsigned head_max[kHeadsPerGroup];
+    const int cpr = D / 8;
+    const QuantShare mine(T, H, cpr, runs);
+    for (int h = threadIdx.x; h < mine.heads; h += kQuantThreads) head_max[h] = 0u;
+    __syncthreads();
+    mine.for_columns([&](int row, int c, int step) {
+        const u32x4* col = x + (size_t)mine.h0 * cpr + c;
+        unsigned m = 0u;
+        for (; row < mine.r1; row += kQuantUnroll * step) {
+            u32x4 raw[kQuantUnroll];
+#pragma unroll
+            for (int j = 0; j < kQuantUnroll; ++j)  // past the end: the last row again, which changes no maximum
+                raw[j] = col[(size_t)min(row + j * step, mine.r1 - 1) * mine.row_chunks];
+#pragma unroll
+            for (int j = 0; j < kQuantUnroll; ++j) m = max(m, chunk_amax_bits(raw[j]));
+        }
+        atomicMax(&head_max[c / cpr], m);
+    });
+    __syncthreads();
+    for (int i = threadIdx.x; i < runs * mine.heads; i += kQuantThreads) {
+        const int h = i % mine.heads;
+        *partial_word(codes, i / mine.heads, (int)blockIdx.x * mine.heads + h, T, H, D, runs, mine.h0, mine.heads) = head_max[h];
     }
 }
 
-
-__global__ __launch_bounds__(256) void quant_encode_kernel(const uint16_t* x, size_t chunks, int chunks_per_row, int H,
-                                                           const unsigned* amax_bits, unsigned char* codes) {
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < chunks; i += (size_t)gridDim.x * blockDim.x) {
-        const int h = (int)((i / chunks_per_row) % H);
-        const float descale = descale_of(amax_bits[h]);
-        *reinterpret_cast<i32x2*>(codes + i * 8) = encode_chunk(*reinterpret_cast<const u32x4*>(x + i * 8), descale);
-    }
+// Maxima of all runs from the workgroup's own part of the code array, then the codes over them.
+__global__ __launch_bounds__(kQuantThreads) void quant_encode_kernel(const u32x4* x, int T, int H, int D, int runs,
+                                                                    unsigned char* codes, float* descale) {
+    __shared__ unsigned head_max[kHeadsPerGroup];
+    const int cpr = D / 8;
+    const QuantShare mine(T, H, cpr, runs);
+    for (int h = threadIdx.x; h < mine.heads; h += kQuantThreads) head_max[h] = 0u;
+    __syncthreads();
+    for (int i = threadIdx.x; i < runs * mine.heads; i += kQuantThreads)
+        atomicMax(&head_max[i % mine.heads],
+                  *partial_word(codes, (int)blockIdx.x, i, T, H, D, runs, mine.h0, mine.heads));
+    __syncthreads();  // every word has been read: the codes may overwrite them
+    if (blockIdx.x == 0)
+        for (int h = threadIdx.x; h < mine.heads; h += kQuantThreads) descale[mine.h0 + h] = descale_of(head_max[h]);
+    mine.for_columns([&](int row, int c, int step) {
+        const size_t col = (size_t)mine.h0 * cpr + c;
+        const Scale s(descale_of(head_max[c / cpr]));
+        for (; row < mine.r1; row += kQuantUnroll * step) {
+            u32x4 raw[kQuantUnroll];
+            size_t at[kQuantUnroll];
+#pragma unroll
+            for (int j = 0; j < kQuantUnroll; ++j) {
+                at[j] = (size_t)min(row + j * step, mine.r1 - 1) * mine.row_chunks + col;
+                raw[j] = x[at[j]];
+            }
+#pragma unroll
+            for (int j = 0; j < kQuantUnroll; ++j)  // past the end: the last row's codes again
+                *reinterpret_cast<i32x2*>(codes + at[j] * 8) = encode_chunk(raw[j], s);
+        }
+    });
 }
 
-__global__ void quant_descale_kernel(float* descale, int H) {
+__global__ void quant_all_zero_kernel(float* descale, int H) {
     const int h = blockIdx.x * blockDim.x + threadIdx.x;
-    if (h < H) {
-        const float s = descale[h] / 448.0f;  // still the maximum here
-        descale[h] = s > 0.0f ? s : 1.0f;
-    }
+    if (h < H) descale[h] = 1.0f;
 }
 
 // Block-wise variant: a block is up to kBlockTokens consecutive tokens of one sample, one head.
@@ -154,19 +229,21 @@ VA_DEV void find_block(const int* cu, int n, int T, int b, int lane, int* r0_out
     *r1_out = min(r1, T);
 }
 
-// Head dimensions up to 256.  Workgroup (b, h): block number b in sample order, head h; wave w takes the
+// Head dimensions up to 256.  A workgroup takes block number b in sample order and head h; wave w takes the
 // rows 32 w .. 32 w + 31 of the block and keeps them in registers (J chunks of 8 values per lane), so x is
 // read once: maximum per wave, the four maxima meet in LDS, then every wave encodes what it holds.
+// Workgroup number (b / 8) 8 H + 8 h + b % 8: the heads of a block follow each other on one XCD, so that their
+// scales, 4 bytes each of the same lines, meet in one L2 instead of reaching memory as partial lines.
 template <int J>
 __global__ __launch_bounds__(256) void quant_blockwise_kernel(const uint16_t* x, const int* cu, int n, int T, int H,
                                                               int chunks_per_row, unsigned char* codes,
                                                               float* descale_tok) {
     __shared__ unsigned wave_max[4];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int h = (int)blockIdx.y;
+    const int h = (int)(blockIdx.x / kXcds) % H;
     int r0, r1;
-    find_block(cu, n, T, (int)blockIdx.x, lane, &r0, &r1);
-    if (r0 >= r1) return;  // the same for the whole workgroup
+    find_block(cu, n, T, (int)(blockIdx.x / (kXcds * (unsigned)H) * kXcds + blockIdx.x % kXcds), lane, &r0, &r1);
+    if (r0 >= r1) return;  // the same for the whole workgroup (the number of blocks is rounded up to the XCDs)
     const int w0 = r0 + 32 * wave;
     const int wrows = max(0, min(32, r1 - w0));  // rows of this wave
     const int chunks = wrows * chunks_per_row;
@@ -194,11 +271,12 @@ __global__ __launch_bounds__(256) void quant_blockwise_kernel(const uint16_t* x,
     if (lane == 0) wave_max[wave] = m;
     __syncthreads();
     const float descale = descale_of(max(max(wave_max[0], wave_max[1]), max(wave_max[2], wave_max[3])));
+    const Scale scale(descale);
 #pragma unroll
     for (int j = 0; j < J; ++j) {
         typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
         const int off = at[j] == (int)0x7ffffff0 ? at[j] : at[j] / 2;
-        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, encode_chunk(raw[j], descale)), dst, off, 0, 0);
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, encode_chunk(raw[j], scale)), dst, off, 0, 0);
     }
     const int r = r0 + 64 * (wave & 1) + lane;  // waves 0 and 1 write the scales of the block's rows
     if (wave < 2 && r < r1) descale_tok[(size_t)r * H + h] = descale;
@@ -227,10 +305,11 @@ __global__ __launch_bounds__(256) void quant_blockwise_two_pass_kernel(const uin
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) m = max(m, (unsigned)__shfl_xor((int)m, d));
     const float descale = descale_of(m);
+    const Scale scale(descale);
     unsigned char* cb = codes + ((size_t)r0 * H + h) * chunks_per_row * 8;
     for (int i = lane; i < chunks; i += 64) {
         const size_t at = ((size_t)(i / chunks_per_row) * row_chunks + i % chunks_per_row) * 8;
-        *reinterpret_cast<i32x2*>(cb + at) = encode_chunk(*reinterpret_cast<const u32x4*>(xb + at), descale);
+        *reinterpret_cast<i32x2*>(cb + at) = encode_chunk(*reinterpret_cast<const u32x4*>(xb + at), scale);
     }
     for (int r = lane; r < rows; r += 64) descale_tok[(size_t)(r0 + r) * H + h] = descale;
 }
@@ -239,18 +318,19 @@ __global__ __launch_bounds__(256) void quant_blockwise_two_pass_kernel(const uin
 
 hipError_t launch_quantize_e4m3(const void* x, int32_t T, int32_t H, int32_t D, void* codes, float* descale,
                                 hipStream_t stream) {
-    const size_t chunks = (size_t)T * H * (D / 8);
-    const unsigned hb = (unsigned)((H + 255) / 256);
-    unsigned* bits = reinterpret_cast<unsigned*>(descale);
-    hipLaunchKernelGGL(quant_clear_kernel, dim3(hb), dim3(256), 0, stream, bits, H);
-    if (chunks > 0) {
-        const unsigned grid = (unsigned)std::min<size_t>((chunks + 255) / 256, 256 * 8);
-        hipLaunchKernelGGL(quant_amax_kernel, dim3(grid), dim3(256), 0, stream, static_cast<const uint16_t*>(x), chunks,
-                           D / 8, H, bits);
-        hipLaunchKernelGGL(quant_encode_kernel, dim3(grid), dim3(256), 0, stream, static_cast<const uint16_t*>(x), chunks,
-                           D / 8, H, bits, static_cast<unsigned char*>(codes));
+    if (T == 0) {
+        hipLaunchKernelGGL(quant_all_zero_kernel, dim3((unsigned)((H + 255) / 256)), dim3(256), 0, stream, descale, H);
+        return hipGetLastError();
     }
-    hipLaunchKernelGGL(quant_descale_kernel, dim3(hb), dim3(256), 0, stream, descale, H);
+    // as many runs as CUs, unless their maxima would not fit the rows of one run: T / runs rows of D bytes
+    // per head against one word per head from every run
+    int32_t runs = std::min(T, kMaxRuns);
+    while (runs > 1 && (int64_t)(T / runs) * D < (int64_t)4 * runs) --runs;
+    const dim3 grid((unsigned)runs, (unsigned)((H + kHeadsPerGroup - 1) / kHeadsPerGroup));
+    const u32x4* xs = static_cast<const u32x4*>(x);
+    unsigned char* cs = static_cast<unsigned char*>(codes);
+    hipLaunchKernelGGL(quant_partial_max_kernel, grid, dim3(kQuantThreads), 0, stream, xs, T, H, D, runs, cs);
+    hipLaunchKernelGGL(quant_encode_kernel, grid, dim3(kQuantThreads), 0, stream, xs, T, H, D, runs, cs, descale);
     return hipGetLastError();
 }
 
@@ -261,13 +341,15 @@ hipError_t launch_quantize_e4m3_blockwise(const void* x, const int32_t* cu_devic
     const uint16_t* xs = static_cast<const uint16_t*>(x);
     unsigned char* cs = static_cast<unsigned char*>(codes);
     const int cpr = D / 8;
-    const dim3 grid((unsigned)num_blocks, (unsigned)H);
+    const int64_t wgs = (int64_t)((num_blocks + kXcds - 1) / kXcds * kXcds) * H;
+    const dim3 grid((unsigned)wgs);
+    const bool one_pass = wgs <= INT32_MAX / 256;
     // a wave holds 32 rows: 32 * cpr chunks over 64 lanes
-    if (cpr <= 8 && H <= 65535)
+    if (cpr <= 8 && one_pass)
         hipLaunchKernelGGL(quant_blockwise_kernel<4>, grid, dim3(256), 0, stream, xs, cu_device, num_seqs, T, H, cpr, cs, descale_tok);
-    else if (cpr <= 16 && H <= 65535)
+    else if (cpr <= 16 && one_pass)
         hipLaunchKernelGGL(quant_blockwise_kernel<8>, grid, dim3(256), 0, stream, xs, cu_device, num_seqs, T, H, cpr, cs, descale_tok);
-    else if (cpr <= 32 && H <= 65535)
+    else if (cpr <= 32 && one_pass)
         hipLaunchKernelGGL(quant_blockwise_kernel<16>, grid, dim3(256), 0, stream, xs, cu_device, num_seqs, T, H, cpr, cs, descale_tok);
     else
         hipLaunchKernelGGL(quant_blockwise_two_pass_kernel, dim3((unsigned)num_blocks, (unsigned)((H + 3) / 4)), dim3(256), 0,
