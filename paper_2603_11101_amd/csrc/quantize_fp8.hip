@@ -92,43 +92,46 @@ VA_DEV i32x2 encode_chunk(u32x4 raw, const Scale& s) {
 // ---------------------------------------------------------------- per-head scales
 
 constexpr int kQuantThreads = 1024;
-constexpr int kQuantUnroll = 4;      // 16-byte loads a thread has in flight
+constexpr int kQuantUnroll = 2;      // 16-byte loads a thread has in flight
 constexpr int kMaxRuns = 256;        // one workgroup per CU; every run leaves its maxima in every other's part
 constexpr int kHeadsPerGroup = 256;  // heads a workgroup handles (their maxima live in LDS)
 
-// The share of workgroup (run i, head group y): token rows [r0, r1), heads [h0, h0 + heads).  A thread
-// stays on one column of 8 values, hence on one head, and walks down the rows.
+// The share of workgroup (run i, head group y): token rows i, i + runs, i + 2 runs, ... and heads
+// [h0, h0 + heads).  A thread stays on one column of 8 values, hence on one head, and walks down the rows.
 struct QuantShare {
-    int r0, r1, h0, heads, columns, rows_at_once;
-    size_t row_chunks;  // chunks of 8 values from one token row to the next
+    int rows, h0, heads, columns, rows_at_once;
+    size_t row_chunks;  // chunks of 8 values from one row of the run to the next
     VA_DEV QuantShare(int T, int H, int cpr, int runs) {
-        r0 = (int)((long long)blockIdx.x * T / runs);
-        r1 = (int)((long long)(blockIdx.x + 1) * T / runs);
+        rows = (T - 1 - (int)blockIdx.x) / runs + 1;
         h0 = (int)blockIdx.y * kHeadsPerGroup;
         heads = min(H - h0, kHeadsPerGroup);
         columns = heads * cpr;
         rows_at_once = max(1, kQuantThreads / columns);
-        row_chunks = (size_t)H * cpr;
+        row_chunks = (size_t)runs * H * cpr;
     }
+    // first chunk of the run
+    VA_DEV size_t first(int H, int cpr) const { return ((size_t)blockIdx.x * H + h0) * cpr; }
     // f(row, chunk column, row step) for the thread's share; threads past the last whole row stay idle
     template <typename F>
     VA_DEV void for_columns(F f) const {
         if ((int)threadIdx.x >= columns * rows_at_once) return;
         for (int c = (int)threadIdx.x % columns; c < columns; c += kQuantThreads)
-            f(r0 + (int)threadIdx.x / columns % rows_at_once, c, rows_at_once);
+            f((int)threadIdx.x / columns % rows_at_once, c, rows_at_once);
     }
 };
 
 // Where word k of the maxima left for run r, head group [h0, h0 + heads) lies in the code array: in the rows of
 // that run and the columns of those heads, row after row, so that only bytes the workgroup (r, y) will
 // write itself are used.  The host chooses the number of runs so that R * heads words fit.
-VA_DEV unsigned* partial_word(unsigned char* codes, int r, int k, int T, int H, int D, int runs, int h0, int heads) {
+VA_DEV unsigned* partial_word(unsigned char* codes, int r, int k, int H, int D, int runs, int h0, int heads) {
     const int words_per_row = heads * D / 4;
-    const int row = (int)((long long)r * T / runs) + k / words_per_row;
-    return reinterpret_cast<unsigned*>(codes + ((size_t)row * H + h0) * D) + k % words_per_row;
+    const size_t row = (size_t)(k / words_per_row) * runs + r;
+    return reinterpret_cast<unsigned*>(codes + (row * H + h0) * D) + k % words_per_row;
 }
 
-// 67 MB (16384 tokens, 16 heads, D = 128): bound by the read.
+// Bound by the read.  A run is every R-th row, so that the workgroups sweep the tensor side by side: with runs of
+// consecutive rows, which start at like addresses, the 67 MB of 16384 tokens x 16 heads x 128 took 20.7 us instead
+// of 17.9, and more loads in flight per thread made it worse (8 instead of 2: 24.8).
 __global__ __launch_bounds__(kQuantThreads) void quant_partial_max_kernel(const u32x4* x, int T, int H, int D, int runs,
                                                                          unsigned char* codes) {
     __shared__ unsigned head_max[kHeadsPerGroup];
@@ -137,13 +140,13 @@ __global__ __launch_bounds__(kQuantThreads) void quant_partial_max_kernel(const 
     for (int h = threadIdx.x; h < mine.heads; h += kQuantThreads) head_max[h] = 0u;
     __syncthreads();
     mine.for_columns([&](int row, int c, int step) {
-        const u32x4* col = x + (size_t)mine.h0 * cpr + c;
+        const u32x4* col = x + mine.first(H, cpr) + c;
         unsigned m = 0u;
-        for (; row < mine.r1; row += kQuantUnroll * step) {
+        for (; row < mine.rows; row += kQuantUnroll * step) {
             u32x4 raw[kQuantUnroll];
 #pragma unroll
             for (int j = 0; j < kQuantUnroll; ++j)  // past the end: the last row again, which changes no maximum
-                raw[j] = col[(size_t)min(row + j * step, mine.r1 - 1) * mine.row_chunks];
+                raw[j] = col[(size_t)min(row + j * step, mine.rows - 1) * mine.row_chunks];
 #pragma unroll
             for (int j = 0; j < kQuantUnroll; ++j) m = max(m, chunk_amax_bits(raw[j]));
         }
@@ -152,7 +155,7 @@ __global__ __launch_bounds__(kQuantThreads) void quant_partial_max_kernel(const 
     __syncthreads();
     for (int i = threadIdx.x; i < runs * mine.heads; i += kQuantThreads) {
         const int h = i % mine.heads;
-        *partial_word(codes, i / mine.heads, (int)blockIdx.x * mine.heads + h, T, H, D, runs, mine.h0, mine.heads) = head_max[h];
+        *partial_word(codes, i / mine.heads, (int)blockIdx.x * mine.heads + h, H, D, runs, mine.h0, mine.heads) = head_max[h];
     }
 }
 
@@ -166,19 +169,19 @@ __global__ __launch_bounds__(kQuantThreads) void quant_encode_kernel(const u32x4
     __syncthreads();
     for (int i = threadIdx.x; i < runs * mine.heads; i += kQuantThreads)
         atomicMax(&head_max[i % mine.heads],
-                  *partial_word(codes, (int)blockIdx.x, i, T, H, D, runs, mine.h0, mine.heads));
+                  *partial_word(codes, (int)blockIdx.x, i, H, D, runs, mine.h0, mine.heads));
     __syncthreads();  // every word has been read: the codes may overwrite them
     if (blockIdx.x == 0)
         for (int h = threadIdx.x; h < mine.heads; h += kQuantThreads) descale[mine.h0 + h] = descale_of(head_max[h]);
     mine.for_columns([&](int row, int c, int step) {
-        const size_t col = (size_t)mine.h0 * cpr + c;
+        const size_t col = mine.first(H, cpr) + c;
         const Scale s(descale_of(head_max[c / cpr]));
-        for (; row < mine.r1; row += kQuantUnroll * step) {
+        for (; row < mine.rows; row += kQuantUnroll * step) {
             u32x4 raw[kQuantUnroll];
             size_t at[kQuantUnroll];
 #pragma unroll
             for (int j = 0; j < kQuantUnroll; ++j) {
-                at[j] = (size_t)min(row + j * step, mine.r1 - 1) * mine.row_chunks + col;
+                at[j] = (size_t)min(row + j * step, mine.rows - 1) * mine.row_chunks + col;
                 raw[j] = x[at[j]];
             }
 #pragma unroll
