@@ -11,9 +11,6 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
-#include <functional>
-#include <map>
-#include <utility>
 #include <vector>
 
 namespace va {
@@ -86,8 +83,60 @@ using namespace va;
 namespace {
 
 struct Keyed {
-    int32_t work;  // inner-loop steps of the item per head (the order of the list)
+    int32_t work;    // inner-loop steps of the item per head (the order of the list)
+    int32_t sample;  // index of its sample
     WorkItem it;
+};
+
+// Heaviest first, ties in the order given: a counting sort where the step counts are small numbers, as they are
+// for every stream but a few items of enormous samples.
+void sort_heaviest_first(std::vector<Keyed>& items) {
+    int32_t top = 0;
+    for (const Keyed& k : items) top = std::max(top, k.work);
+    if ((size_t)top > 4 * items.size() + 1024) {
+        std::stable_sort(items.begin(), items.end(), [](const Keyed& a, const Keyed& b) { return a.work > b.work; });
+        return;
+    }
+    std::vector<int32_t> at((size_t)top + 2, 0);  // at[top - work + 1] counts, then at[top - work] is the next place
+    for (const Keyed& k : items) ++at[(size_t)(top - k.work) + 1];
+    for (size_t i = 1; i < at.size(); ++i) at[i] += at[i - 1];
+    std::vector<Keyed> sorted(items.size());
+    for (const Keyed& k : items) sorted[(size_t)at[(size_t)(top - k.work)]++] = k;
+    items.swap(sorted);
+}
+
+// Least-loaded-first queue of workgroups (ties: lowest index): a binary heap of (load, index) in one word each,
+// in which the workgroup at the top takes the next work and sinks to its new place.
+class LeastLoaded {
+public:
+    // workgroups first, first + step, ... below end, all idle
+    LeastLoaded(int32_t first, int32_t end, int32_t step) {
+        for (int32_t w = first; w < end; w += step) heap_.push_back((uint64_t)w);  // equal loads, ascending: a heap
+    }
+    // gives the least-loaded workgroup a work of this cost: returns its index
+    int32_t give(int64_t cost) {
+        const uint64_t key = heap_[0] + ((uint64_t)cost << kIndexBits);
+        const int32_t who = (int32_t)(key & ((1u << kIndexBits) - 1));
+        last_finish_ = std::max(last_finish_, (int64_t)(key >> kIndexBits));
+        const size_t n = heap_.size();
+        size_t i = 0;
+        for (;;) {
+            size_t c = 2 * i + 1;
+            if (c >= n) break;
+            if (c + 1 < n && heap_[c + 1] < heap_[c]) ++c;
+            if (heap_[c] >= key) break;
+            heap_[i] = heap_[c];
+            i = c;
+        }
+        heap_[i] = key;
+        return who;
+    }
+    int64_t last_finish() const { return last_finish_; }  // largest load so far
+
+private:
+    static constexpr int kIndexBits = 16;  // workgroups of a launch stay far below 2^16, loads below 2^48
+    std::vector<uint64_t> heap_;
+    int64_t last_finish_ = 0;
 };
 
 // dK/dV pass: one workgroup runs one work, and the hardware hands the works to free workgroup slots in list
@@ -100,28 +149,22 @@ struct Keyed {
 void split_late_tiles(std::vector<Keyed>& items, std::vector<WorkItem>& merges, int32_t G, int32_t Hkv,
                       int32_t slots, int32_t max_slots) {
     auto cost = [&](const Keyed& k) { return (int64_t)k.work * G + kWorkFixedCost; };
-    auto heavier = [](const Keyed& a, const Keyed& b) { return a.work > b.work; };
     int32_t used = 0;
-    std::vector<int64_t> heap;
     for (int32_t round = 0; round < max_slots; ++round) {
-        std::stable_sort(items.begin(), items.end(), heavier);
+        sort_heaviest_first(items);
         int64_t total = 0, heaviest = 0, last_finish = 0;
         int32_t last_item = -1;
-        heap.assign((size_t)slots, 0);  // min-heap of slot loads (all zero: already a heap)
-        for (size_t i = 0; i < items.size(); ++i)
-            for (int32_t g = 0; g < Hkv; ++g) {
-                const int64_t c = cost(items[i]);
-                std::pop_heap(heap.begin(), heap.end(), std::greater<int64_t>());
-                const int64_t finish = heap.back() + c;
-                heap.back() = finish;
-                std::push_heap(heap.begin(), heap.end(), std::greater<int64_t>());
-                total += c;
-                heaviest = std::max(heaviest, c);
-                if (finish > last_finish) {
-                    last_finish = finish;
-                    last_item = (int32_t)i;
-                }
+        LeastLoaded queue(0, slots, 1);
+        for (size_t i = 0; i < items.size(); ++i) {
+            const int64_t c = cost(items[i]);
+            for (int32_t g = 0; g < Hkv; ++g) queue.give(c);
+            total += c * Hkv;
+            heaviest = std::max(heaviest, c);
+            if (queue.last_finish() > last_finish) {
+                last_finish = queue.last_finish();
+                last_item = (int32_t)i;
             }
+        }
         if (last_item < 0) return;
         const int64_t bound = std::max((total + slots - 1) / slots, heaviest);
         if (last_finish * 100 <= bound * (used == 0 ? 110 : 104)) return;
@@ -251,6 +294,9 @@ int va_build_worklist(const int32_t* cu, const int32_t* prefix_lens, int32_t n,
 
     std::vector<Keyed> items;
     std::vector<WorkItem> merges;
+    // Forward and dQ: where every query tile of a sample costs the same (no causal structure: whole samples
+    // visible), the plain order below already walks the tiles of a sample one after the other, i.e. is local by itself.
+    bool tiles_differ = false;
     for (int32_t s = 0; s < n; ++s) {
         const int32_t c = cu[s], L = cu[s + 1] - c;
         int32_t P, P2;
@@ -276,9 +322,10 @@ int va_build_worklist(const int32_t* cu, const int32_t* prefix_lens, int32_t n,
                     qt_end = (int32_t)(last_row / bn) + 1;
                 }
                 WorkItem it = {{c + j0, std::min(bm, L - j0), c, qt_first, qt_end - qt_first, P2, P, L}};
-                items.push_back({it.w[4], it});
+                items.push_back({it.w[4], s, it});
             }
         } else {
+            const size_t first_of_sample = items.size();
             for (int32_t r0 = 0; r0 < L; r0 += bm) {
                 const int32_t rows = std::min(bm, L - r0);
                 const int32_t kv_len = visible(r0 + rows - 1, L, Pm, P2m, mask_mode);
@@ -286,13 +333,14 @@ int va_build_worklist(const int32_t* cu, const int32_t* prefix_lens, int32_t n,
                 const int32_t n_full = visible(r0, L, Pm, P2m, mask_mode) / bn;
                 WorkItem it = {{c + r0, rows, c, P2, n_full, n_tiles, P, L}};
                 // under the sliding window the key tiles below the first row's window are not visited
-                items.push_back({n_tiles - first_visible(r0, Pm, mask_mode) / bn, it});
+                items.push_back({n_tiles - first_visible(r0, Pm, mask_mode) / bn, s, it});
+                tiles_differ = tiles_differ || items.back().work != items[first_of_sample].work;
             }
         }
     }
     if (pass == VA_PASS_BWD_DKDV)
         split_late_tiles(items, merges, Hq / Hkv, Hkv, persistent_workgroups(pass, D), max_partial_slots(D, Hkv));
-    std::stable_sort(items.begin(), items.end(), [](const Keyed& a, const Keyed& b) { return a.work > b.work; });
+    sort_heaviest_first(items);
     const WorklistLayout lay = worklist_layout(pass, D, Hq, Hkv, (int32_t)items.size(), (int32_t)merges.size());
     WorkItem* out = static_cast<WorkItem*>(host_out);
     std::memset(out, 0, need);
@@ -306,58 +354,35 @@ int va_build_worklist(const int32_t* cu, const int32_t* prefix_lens, int32_t n,
     // part; items are sorted by cost and every work of an item costs the same, so id order is cost order.
     const int32_t G = Hq / Hkv;
     const int32_t P = lay.num_workgroups;
-    std::vector<int64_t> load((size_t)P, 0);
-    std::vector<std::vector<int32_t>> mine((size_t)P);
-    auto cost_of = [&](int32_t id) {
-        return (int64_t)items[id / lay.works_per_item].work * (pass == VA_PASS_BWD_DKDV ? G : 1) + kWorkFixedCost;
+    const int32_t per_item = lay.works_per_item;
+    auto cost_of_item = [&](int32_t i) {
+        return (int64_t)items[i].work * (pass == VA_PASS_BWD_DKDV ? G : 1) + kWorkFixedCost;
     };
-    // Where every query tile of a sample costs the same (no causal structure: whole samples visible), the
-    // plain order below already walks the tiles of a sample one after the other, i.e. is local by itself.
-    bool tiles_differ = false;
-    {
-        std::map<int32_t, int32_t> cost_of_sample;  // first row of the sample -> cost of the first of its items seen
-        for (const Keyed& k : items) {
-            const auto at = cost_of_sample.emplace(k.it.w[2], k.work).first;
-            tiles_differ = tiles_differ || at->second != k.work;
-        }
-    }
-    if (tiles_differ && pass != VA_PASS_BWD_DKDV && P % kXcds == 0) {
-        // Forward and dQ: all works of one (sample, KV head) stream the same K and V rows.  Workgroup b runs
-        // on XCD b % 8, and each XCD has an L2 of its own, so those works are given to workgroups of one XCD
-        // and placed at about the same position of their queues: they then run at about the same time and
-        // the rows are fetched into that L2 once instead of once per work.  Groups go to the XCDs, and
-        // the works of a group to the workgroups of its XCD, longest processing time first; groups heavier
-        // than a sixteenth of an XCD's share are cut into runs of consecutive query tiles first, so that
-        // few heavy groups (one KV head, long samples) still balance.
-        struct Group {
-            int64_t cost = 0;
-            std::vector<int32_t> works;
-        };
-        const int32_t chunks_per_head = lay.works_per_item / Hkv;  // head chunks that share one KV head
-        int64_t total = 0;
-        for (int32_t id = 0; id < lay.num_works; ++id) total += cost_of(id);
-        const int64_t cap = std::max<int64_t>(1, total / (kXcds * 16));
-        std::vector<Group> groups;
-        {
-            std::map<std::pair<int32_t, int32_t>, int32_t> open;  // (sample's first row, KV head) -> its current group
-            for (int32_t id = 0; id < lay.num_works; ++id) {
-                const int32_t g = (id % lay.works_per_item) / chunks_per_head;
-                const std::pair<int32_t, int32_t> key(items[id / lay.works_per_item].it.w[2], g);
-                auto at = open.find(key);
-                if (at == open.end() || groups[at->second].cost + cost_of(id) > cap) {
-                    open[key] = (int32_t)groups.size();
-                    groups.emplace_back();
-                    at = open.find(key);
-                }
-                groups[at->second].cost += cost_of(id);
-                groups[at->second].works.push_back(id);
-            }
-        }
+    // the works in the order they are assigned, and the workgroup of each
+    std::vector<int32_t> assigned, owner;
+    assigned.reserve((size_t)lay.num_works);
+    owner.reserve((size_t)lay.num_works);
+    auto assign = [&](int32_t id, int32_t w) {
+        assigned.push_back(id);
+        owner.push_back(w);
+    };
+    struct Group {  // works of one (sample, KV head), or a part of them
+        int64_t cost = 0;
+        int32_t first = -1, last = -1;  // chain through next_in_group
+    };
+    std::vector<int32_t> next_in_group;
+    auto append = [&](Group& g, int32_t id, int64_t cost) {
+        g.cost += cost;
+        if (g.first < 0) g.first = id;
+        else next_in_group[g.last] = id;
+        g.last = id;
+    };
+    // group indices, costliest first (ties: ascending), dealt to the XCDs, each to the least loaded one
+    auto deal_to_xcds = [&](const std::vector<Group>& groups, std::vector<int32_t> (&of_xcd)[kXcds]) {
         std::vector<int32_t> order(groups.size());
         for (size_t i = 0; i < order.size(); ++i) order[i] = (int32_t)i;
         std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) { return groups[a].cost > groups[b].cost; });
         int64_t xcd_load[kXcds] = {};
-        std::vector<int32_t> of_xcd[kXcds];
         for (int32_t gi : order) {
             int32_t x = 0;
             for (int32_t c = 1; c < kXcds; ++c)
@@ -365,18 +390,40 @@ int va_build_worklist(const int32_t* cu, const int32_t* prefix_lens, int32_t n,
             xcd_load[x] += groups[gi].cost;
             of_xcd[x].push_back(gi);
         }
-        auto heavier = [&](int32_t a, int32_t b) { return load[a] != load[b] ? load[a] > load[b] : a > b; };
-        for (int32_t x = 0; x < kXcds; ++x) {
-            std::vector<int32_t> heap;  // min-heap on (load, index) over the workgroups of this XCD
-            for (int32_t w = x; w < P; w += kXcds) heap.push_back(w);
-            for (int32_t gi : of_xcd[x])
-                for (int32_t id : groups[gi].works) {
-                    std::pop_heap(heap.begin(), heap.end(), heavier);
-                    const int32_t w = heap.back();
-                    load[w] += cost_of(id);
-                    mine[w].push_back(id);
-                    std::push_heap(heap.begin(), heap.end(), heavier);
+    };
+    if (tiles_differ && P % kXcds == 0) {
+        // Forward and dQ: all works of one (sample, KV head) stream the same K and V rows.  Workgroup b runs
+        // on XCD b % 8, and each XCD has an L2 of its own, so those works are given to workgroups of one XCD
+        // and placed at about the same position of their queues: they then run at about the same time and
+        // the rows are fetched into that L2 once instead of once per work.  Groups go to the XCDs, and
+        // the works of a group to the workgroups of its XCD, longest processing time first; groups heavier
+        // than a sixteenth of an XCD's share are cut into runs of consecutive query tiles first, so that
+        // few heavy groups (one KV head, long samples) still balance.
+        const int32_t chunks_per_head = per_item / Hkv;  // head chunks that share one KV head
+        int64_t total = 0;
+        for (int32_t i = 0; i < lay.num_items; ++i) total += cost_of_item(i) * per_item;
+        const int64_t cap = std::max<int64_t>(1, total / (kXcds * 16));
+        next_in_group.assign((size_t)lay.num_works, -1);
+        std::vector<Group> groups;
+        std::vector<int32_t> open((size_t)n * Hkv, -1);  // (sample, KV head) -> its current group
+        for (int32_t i = 0; i < lay.num_items; ++i) {
+            const int64_t cost = cost_of_item(i);
+            for (int32_t chunk = 0; chunk < per_item; ++chunk) {
+                int32_t& at = open[(size_t)items[i].sample * Hkv + chunk / chunks_per_head];
+                if (at < 0 || groups[at].cost + cost > cap) {
+                    at = (int32_t)groups.size();
+                    groups.emplace_back();
                 }
+                append(groups[at], i * per_item + chunk, cost);
+            }
+        }
+        std::vector<int32_t> of_xcd[kXcds];
+        deal_to_xcds(groups, of_xcd);
+        for (int32_t x = 0; x < kXcds; ++x) {
+            LeastLoaded queue(x, P, kXcds);
+            for (int32_t gi : of_xcd[x])
+                for (int32_t id = groups[gi].first; id >= 0; id = next_in_group[id])
+                    assign(id, queue.give(cost_of_item(id / per_item)));
         }
     } else if (pass == VA_PASS_BWD_DKDV) {
         // One work per workgroup; workgroup b of the launch runs on XCD b % 8 and takes the work at position b
@@ -391,34 +438,25 @@ int va_build_worklist(const int32_t* cu, const int32_t* prefix_lens, int32_t n,
         std::vector<int32_t> order((size_t)lay.num_works);
         for (int32_t id = 0; id < lay.num_works; ++id) order[id] = id;
         if (P % kXcds == 0 && lay.num_works >= 4 * P) {
-            struct Group {
-                int64_t cost = 0;
-                std::vector<int32_t> works;
-            };
-            std::map<std::pair<int32_t, int32_t>, int32_t> index;  // (sample's first row, KV head) -> group
+            next_in_group.assign((size_t)lay.num_works, -1);
             std::vector<Group> groups;
-            for (int32_t id = 0; id < lay.num_works; ++id) {
-                const std::pair<int32_t, int32_t> key(items[id / lay.works_per_item].it.w[2], id % lay.works_per_item);
-                auto at = index.find(key);
-                if (at == index.end()) {
-                    at = index.emplace(key, (int32_t)groups.size()).first;
-                    groups.emplace_back();
+            std::vector<int32_t> index((size_t)n * Hkv, -1);  // (sample, KV head) -> group
+            for (int32_t i = 0; i < lay.num_items; ++i) {
+                const int64_t cost = cost_of_item(i);
+                for (int32_t g = 0; g < per_item; ++g) {
+                    int32_t& at = index[(size_t)items[i].sample * Hkv + g];
+                    if (at < 0) {
+                        at = (int32_t)groups.size();
+                        groups.emplace_back();
+                    }
+                    append(groups[at], i * per_item + g, cost);
                 }
-                groups[at->second].cost += cost_of(id);
-                groups[at->second].works.push_back(id);
             }
-            std::vector<int32_t> by_cost(groups.size());
-            for (size_t i = 0; i < by_cost.size(); ++i) by_cost[i] = (int32_t)i;
-            std::stable_sort(by_cost.begin(), by_cost.end(), [&](int32_t a, int32_t b) { return groups[a].cost > groups[b].cost; });
-            int64_t xcd_load[kXcds] = {};
-            std::vector<int32_t> queue[kXcds];
-            for (int32_t gi : by_cost) {
-                int32_t x = 0;
-                for (int32_t c = 1; c < kXcds; ++c)
-                    if (xcd_load[c] < xcd_load[x]) x = c;
-                xcd_load[x] += groups[gi].cost;
-                queue[x].insert(queue[x].end(), groups[gi].works.begin(), groups[gi].works.end());
-            }
+            std::vector<int32_t> of_xcd[kXcds], queue[kXcds];
+            deal_to_xcds(groups, of_xcd);
+            for (int32_t x = 0; x < kXcds; ++x)
+                for (int32_t gi : of_xcd[x])
+                    for (int32_t id = groups[gi].first; id >= 0; id = next_in_group[id]) queue[x].push_back(id);
             // position 8 k + x is the k-th work of XCD x; an XCD that has run out takes from the end of the
             // queue that has most left
             std::vector<int32_t> local;
@@ -437,15 +475,11 @@ int va_build_worklist(const int32_t* cu, const int32_t* prefix_lens, int32_t n,
             }
             // replay of the dispatch: every XCD hands its positions, in order, to the least-loaded of its slots
             auto finish_time = [&](const std::vector<int32_t>& ord) {
-                const int32_t per_xcd = P / kXcds;
-                std::vector<int64_t> heap((size_t)P, 0);  // kXcds min-heaps of per_xcd slot loads
                 int64_t finish = 0;
-                for (int32_t pos = 0; pos < lay.num_works; ++pos) {
-                    const auto first = heap.begin() + (pos % kXcds) * per_xcd, last = first + per_xcd;
-                    std::pop_heap(first, last, std::greater<int64_t>());
-                    *(last - 1) += cost_of(ord[pos]);
-                    finish = std::max(finish, *(last - 1));
-                    std::push_heap(first, last, std::greater<int64_t>());
+                for (int32_t x = 0; x < kXcds; ++x) {
+                    LeastLoaded slots(0, P / kXcds, 1);
+                    for (int32_t pos = x; pos < lay.num_works; pos += kXcds) slots.give(cost_of_item(ord[pos] / per_item));
+                    finish = std::max(finish, slots.last_finish());
                 }
                 return finish;
             };
@@ -456,37 +490,31 @@ int va_build_worklist(const int32_t* cu, const int32_t* prefix_lens, int32_t n,
         }
         // the table is not used by this pass; it holds the order in equal runs so that it still partitions the ids
         const int32_t per = std::max(1, (lay.num_works + P - 1) / P);
-        for (int32_t i = 0; i < lay.num_works; ++i) mine[i / per].push_back(order[i]);
+        for (int32_t i = 0; i < lay.num_works; ++i) assign(order[i], i / per);
     } else {
         // Longest processing time first: works in descending cost order (ties: ascending id), each to the
         // least-loaded workgroup (ties: lowest index).
-        auto heavier = [&](int32_t a, int32_t b) { return load[a] != load[b] ? load[a] > load[b] : a > b; };
-        std::vector<int32_t> heap((size_t)P);
-        for (int32_t w = 0; w < P; ++w) heap[w] = w;  // min-heap on (load, index); all loads 0: already a heap
-        for (int32_t id = 0; id < lay.num_works; ++id) {
-            std::pop_heap(heap.begin(), heap.end(), heavier);
-            const int32_t w = heap.back();
-            load[w] += cost_of(id);
-            mine[w].push_back(id);
-            std::push_heap(heap.begin(), heap.end(), heavier);
-        }
+        LeastLoaded queue(0, P, 1);
+        for (int32_t id = 0; id < lay.num_works; ++id) assign(id, queue.give(cost_of_item(id / per_item)));
     }
     int32_t* table = out[lay.table_rec].w;
     int32_t* ids = out[lay.id_rec].w;
-    int32_t at = 0;
+    std::vector<int32_t> at((size_t)P + 1, 0);  // first schedule position of each workgroup
+    for (int32_t w : owner) ++at[(size_t)w + 1];
+    for (int32_t w = 0; w < P; ++w) at[(size_t)w + 1] += at[w];
     for (int32_t w = 0; w < P; ++w) {
         int32_t* e = table + kTableWordsPerWorkgroup * w;
-        const int32_t count = (int32_t)mine[w].size();
-        for (int32_t i = 0; i < kTableWordsPerWorkgroup; ++i) e[i] = 0;
-        if (count > 0) {
-            const WorkItem& first = items[mine[w][0] / lay.works_per_item].it;
-            for (int32_t i = 0; i < 8; ++i) e[i] = first.w[i];
-            e[8] = mine[w][0];
-            e[9] = mine[w][count > 1 ? 1 : 0];
-        }
-        e[10] = at;
-        e[11] = count;
-        for (int32_t id : mine[w]) ids[at++] = id;
+        e[10] = at[w];
+        e[11] = at[(size_t)w + 1] - at[w];
+    }
+    for (size_t i = 0; i < assigned.size(); ++i) ids[at[owner[i]]++] = assigned[i];  // assignment order inside a workgroup
+    for (int32_t w = 0; w < P; ++w) {
+        int32_t* e = table + kTableWordsPerWorkgroup * w;
+        if (e[11] == 0) continue;
+        const int32_t* mine = ids + e[10];
+        std::memcpy(e, items[mine[0] / per_item].it.w, 8 * sizeof(int32_t));
+        e[8] = mine[0];
+        e[9] = mine[e[11] > 1 ? 1 : 0];
     }
     *num_items = lay.num_items;
     return VA_OK;
