@@ -43,6 +43,18 @@ def _load():
     lib.va_last_error.restype = ctypes.c_char_p
     lib.varlen_attn_bwd_workspace_bytes.restype = ctypes.c_size_t
     lib.varlen_attn_bwd_workspace_bytes.argtypes = [ctypes.POINTER(va_shape)]
+    # argument types of the calls a program makes on every layer: plain integers then pass as pointers, without a
+    # ctypes object for each (half of the host time of a call on a tiny stream)
+    ptr, i32, f32, size, shape = ctypes.c_void_p, ctypes.c_int32, ctypes.c_float, ctypes.c_size_t, ctypes.POINTER(va_shape)
+    bwd = [ptr] * 12 + [shape, f32] + [ptr] * 3
+    lib.varlen_attn_fwd.argtypes = [ptr] * 7 + [shape, f32] + [ptr] * 3
+    lib.varlen_attn_bwd.argtypes = bwd + [ptr, size, ptr]
+    lib.varlen_attn_bwd_static.argtypes = bwd + [ptr]
+    lib.varlen_attn_bwd_stages.argtypes = bwd + [ptr, size, ptr, ctypes.c_uint32]
+    lib.varlen_attn_fwd_fp8.argtypes = [ptr] * 10 + [shape, f32] + [ptr] * 3
+    lib.varlen_attn_fwd_fp8_blockwise.argtypes = lib.varlen_attn_fwd_fp8.argtypes
+    lib.va_quantize_e4m3_per_head_device.argtypes = [ptr, i32, i32, i32, ptr, ptr, ptr]
+    lib.va_quantize_e4m3_blockwise_device.argtypes = [ptr, ptr, ptr, i32, i32, i32, ptr, ptr, ptr]
     return lib
 
 
@@ -86,10 +98,18 @@ def _ptr(a):
     return ctypes.c_void_p(a.data_ptr())
 
 
+def _addr(a):
+    """Address of a numpy array or a torch tensor as an integer, or None."""
+    if a is None:
+        return None
+    return a.ctypes.data if isinstance(a, np.ndarray) else a.data_ptr()
+
+
 def _stream_ptr(stream):
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+    if stream is not None:
+        return stream.cuda_stream
+    # the handle alone: building torch's stream object around it takes 2.7 us, a third of a whole call
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def va_last_error() -> str:
@@ -145,7 +165,7 @@ def va_build_worklist(cu_seqlens, prefix_lens, mask_mode, pass_id, head_dim, num
     cu = _i32(cu_seqlens)
     pl = _prefix(prefix_lens, mask_mode, len(cu) - 1)
     nbytes = va_worklist_size(cu, pass_id, head_dim, num_q_heads, num_kv_heads)
-    buf = np.zeros((nbytes // 32, 8), dtype=np.int32)
+    buf = np.empty((nbytes // 32, 8), dtype=np.int32)  # the library clears it
     n_items = ctypes.c_int32(0)
     _check(_lib.va_build_worklist(_ptr(cu), _ptr(pl), ctypes.c_int32(len(cu) - 1), ctypes.c_int32(mask_mode),
                                   ctypes.c_int32(pass_id), ctypes.c_int32(head_dim), ctypes.c_int32(num_q_heads),
@@ -202,8 +222,7 @@ def va_quantize_e4m3_per_head_device(x, codes, descale, stream=None):
     """x: bfloat16 device tensor [T, H, D]; codes: uint8 device tensor [T, H, D]; descale: float32 device
     tensor [H].  Enqueues the quantisation on the stream."""
     T, H, D = x.shape
-    _check(_lib.va_quantize_e4m3_per_head_device(_ptr(x), ctypes.c_int32(T), ctypes.c_int32(H), ctypes.c_int32(D),
-                                                 _ptr(codes), _ptr(descale), _stream_ptr(stream)))
+    _check(_lib.va_quantize_e4m3_per_head_device(_addr(x), T, H, D, _addr(codes), _addr(descale), _stream_ptr(stream)))
 
 
 def va_quantize_e4m3_blockwise(x_bf16_bits, cu_seqlens):
@@ -230,9 +249,8 @@ def va_quantize_e4m3_blockwise_device(x, cu_seqlens, cu_seqlens_device, codes, d
     if T != int(cu[-1]) or cu_seqlens_device.numel() != len(cu) or tuple(codes.shape) != (T, H, D) \
             or tuple(descale_tok.shape) != (T, H):
         raise ValueError("shapes of x, cu_seqlens, codes and descale_tok disagree")
-    _check(_lib.va_quantize_e4m3_blockwise_device(_ptr(x), _ptr(cu), _ptr(cu_seqlens_device), ctypes.c_int32(len(cu) - 1),
-                                                  ctypes.c_int32(H), ctypes.c_int32(D), _ptr(codes), _ptr(descale_tok),
-                                                  _stream_ptr(stream)))
+    _check(_lib.va_quantize_e4m3_blockwise_device(_addr(x), _addr(cu), _addr(cu_seqlens_device), len(cu) - 1, H, D,
+                                                  _addr(codes), _addr(descale_tok), _stream_ptr(stream)))
 
 
 def make_shape(total_tokens, num_seqs, num_q_heads, num_kv_heads, head_dim, max_seqlen, mask_mode):
@@ -248,31 +266,54 @@ def va_bwd_has_delta_kernel(head_dim):
     return bool(_lib.va_bwd_has_delta_kernel(ctypes.c_int32(head_dim)))
 
 
+# The device calls.  The underscored forms take the host arrays as addresses: PackedStream, which keeps its arrays,
+# looks those up once.
+
+def _fwd(q, k, v, cu, pl, worklist, wl_host, shape, scale, out, lse, stream):
+    _check(_lib.varlen_attn_fwd(_addr(q), _addr(k), _addr(v), cu, pl, _addr(worklist), wl_host, shape, scale, _addr(out),
+                                _addr(lse), _stream_ptr(stream)))
+
+
+def _bwd_args(q, k, v, out, lse, dout, cu, pl, worklist_dkdv, dkdv_host, worklist_dq, dq_host, shape, scale, dq, dk, dv):
+    return (_addr(q), _addr(k), _addr(v), _addr(out), _addr(lse), _addr(dout), cu, pl, _addr(worklist_dkdv), dkdv_host,
+            _addr(worklist_dq), dq_host, shape, scale, _addr(dq), _addr(dk), _addr(dv))
+
+
+def _fwd_fp8(call, q8, k8, v8, q_descale, k_descale, v_descale, cu, pl, worklist, wl_host, shape, scale, out, lse, stream):
+    _check(call(_addr(q8), _addr(k8), _addr(v8), _addr(q_descale), _addr(k_descale), _addr(v_descale), cu, pl,
+                _addr(worklist), wl_host, shape, scale, _addr(out), _addr(lse), _stream_ptr(stream)))
+
+
+def _check_token_scales(shape, q_descale_tok, k_descale_tok, v_descale_tok):
+    T = int(shape.total_tokens)
+    for name, d, h in (("q", q_descale_tok, shape.num_q_heads), ("k", k_descale_tok, shape.num_kv_heads),
+                       ("v", v_descale_tok, shape.num_kv_heads)):
+        if d is not None and tuple(d.shape) != (T, h):  # the library cannot see the arrays' lengths
+            raise ValueError(f"{name}_descale_tok has shape {tuple(d.shape)}, expected {(T, h)}")
+
+
 def varlen_attn_fwd(q, k, v, cu_seqlens, prefix_lens, worklist, worklist_host, shape, scale, out, lse, stream=None):
     cu = _i32(cu_seqlens)
     pl = _prefix(prefix_lens, shape.mask_mode, len(cu) - 1)
-    _check(_lib.varlen_attn_fwd(_ptr(q), _ptr(k), _ptr(v), _ptr(cu), _ptr(pl), _ptr(worklist), _ptr(worklist_host),
-                                ctypes.byref(shape), ctypes.c_float(scale), _ptr(out), _ptr(lse), _stream_ptr(stream)))
+    _fwd(q, k, v, _addr(cu), _addr(pl), worklist, _addr(worklist_host), shape, scale, out, lse, stream)
 
 
 def varlen_attn_bwd(q, k, v, out, lse, dout, cu_seqlens, prefix_lens, worklist_dkdv, worklist_dkdv_host,
                     worklist_dq, worklist_dq_host, shape, scale, dq, dk, dv, workspace, workspace_bytes, stream=None):
     cu = _i32(cu_seqlens)
     pl = _prefix(prefix_lens, shape.mask_mode, len(cu) - 1)
-    _check(_lib.varlen_attn_bwd(_ptr(q), _ptr(k), _ptr(v), _ptr(out), _ptr(lse), _ptr(dout), _ptr(cu), _ptr(pl),
-                                _ptr(worklist_dkdv), _ptr(worklist_dkdv_host), _ptr(worklist_dq), _ptr(worklist_dq_host),
-                                ctypes.byref(shape), ctypes.c_float(scale), _ptr(dq), _ptr(dk), _ptr(dv),
-                                _ptr(workspace), ctypes.c_size_t(workspace_bytes), _stream_ptr(stream)))
+    _check(_lib.varlen_attn_bwd(*_bwd_args(q, k, v, out, lse, dout, _addr(cu), _addr(pl), worklist_dkdv,
+                                           _addr(worklist_dkdv_host), worklist_dq, _addr(worklist_dq_host), shape, scale,
+                                           dq, dk, dv), _addr(workspace), workspace_bytes, _stream_ptr(stream)))
 
 
 def varlen_attn_bwd_static(q, k, v, out, lse, dout, cu_seqlens, prefix_lens, worklist_dkdv, worklist_dkdv_host,
                            worklist_dq, worklist_dq_host, shape, scale, dq, dk, dv, stream=None):
     cu = _i32(cu_seqlens)
     pl = _prefix(prefix_lens, shape.mask_mode, len(cu) - 1)
-    _check(_lib.varlen_attn_bwd_static(_ptr(q), _ptr(k), _ptr(v), _ptr(out), _ptr(lse), _ptr(dout), _ptr(cu), _ptr(pl),
-                                       _ptr(worklist_dkdv), _ptr(worklist_dkdv_host), _ptr(worklist_dq),
-                                       _ptr(worklist_dq_host), ctypes.byref(shape), ctypes.c_float(scale),
-                                       _ptr(dq), _ptr(dk), _ptr(dv), _stream_ptr(stream)))
+    _check(_lib.varlen_attn_bwd_static(*_bwd_args(q, k, v, out, lse, dout, _addr(cu), _addr(pl), worklist_dkdv,
+                                                  _addr(worklist_dkdv_host), worklist_dq, _addr(worklist_dq_host), shape,
+                                                  scale, dq, dk, dv), _stream_ptr(stream)))
 
 
 def varlen_attn_bwd_stages(q, k, v, out, lse, dout, cu_seqlens, prefix_lens, worklist_dkdv, worklist_dkdv_host,
@@ -280,35 +321,52 @@ def varlen_attn_bwd_stages(q, k, v, out, lse, dout, cu_seqlens, prefix_lens, wor
                            stages, stream=None):
     cu = _i32(cu_seqlens)
     pl = _prefix(prefix_lens, shape.mask_mode, len(cu) - 1)
-    _check(_lib.varlen_attn_bwd_stages(_ptr(q), _ptr(k), _ptr(v), _ptr(out), _ptr(lse), _ptr(dout), _ptr(cu), _ptr(pl),
-                                       _ptr(worklist_dkdv), _ptr(worklist_dkdv_host), _ptr(worklist_dq),
-                                       _ptr(worklist_dq_host), ctypes.byref(shape), ctypes.c_float(scale),
-                                       _ptr(dq), _ptr(dk), _ptr(dv), _ptr(workspace), ctypes.c_size_t(workspace_bytes),
-                                       _stream_ptr(stream), ctypes.c_uint32(stages)))
+    _check(_lib.varlen_attn_bwd_stages(*_bwd_args(q, k, v, out, lse, dout, _addr(cu), _addr(pl), worklist_dkdv,
+                                                  _addr(worklist_dkdv_host), worklist_dq, _addr(worklist_dq_host), shape,
+                                                  scale, dq, dk, dv), _addr(workspace), workspace_bytes,
+                                       _stream_ptr(stream), stages))
 
 
 def varlen_attn_fwd_fp8(q8, k8, v8, q_descale, k_descale, v_descale, cu_seqlens, prefix_lens, worklist, worklist_host,
                         shape, scale, out, lse, stream=None):
     cu = _i32(cu_seqlens)
     pl = _prefix(prefix_lens, shape.mask_mode, len(cu) - 1)
-    _check(_lib.varlen_attn_fwd_fp8(_ptr(q8), _ptr(k8), _ptr(v8), _ptr(q_descale), _ptr(k_descale), _ptr(v_descale),
-                                    _ptr(cu), _ptr(pl), _ptr(worklist), _ptr(worklist_host), ctypes.byref(shape),
-                                    ctypes.c_float(scale), _ptr(out), _ptr(lse), _stream_ptr(stream)))
+    _fwd_fp8(_lib.varlen_attn_fwd_fp8, q8, k8, v8, q_descale, k_descale, v_descale, _addr(cu), _addr(pl), worklist,
+             _addr(worklist_host), shape, scale, out, lse, stream)
 
 
 def varlen_attn_fwd_fp8_blockwise(q8, k8, v8, q_descale_tok, k_descale_tok, v_descale_tok, cu_seqlens, prefix_lens,
                                   worklist, worklist_host, shape, scale, out, lse, stream=None):
     cu = _i32(cu_seqlens)
     pl = _prefix(prefix_lens, shape.mask_mode, len(cu) - 1)
-    T = int(shape.total_tokens)
-    for name, d, h in (("q", q_descale_tok, shape.num_q_heads), ("k", k_descale_tok, shape.num_kv_heads),
-                       ("v", v_descale_tok, shape.num_kv_heads)):
-        if d is not None and tuple(d.shape) != (T, h):  # the library cannot see the arrays' lengths
-            raise ValueError(f"{name}_descale_tok has shape {tuple(d.shape)}, expected {(T, h)}")
-    _check(_lib.varlen_attn_fwd_fp8_blockwise(_ptr(q8), _ptr(k8), _ptr(v8), _ptr(q_descale_tok), _ptr(k_descale_tok),
-                                              _ptr(v_descale_tok), _ptr(cu), _ptr(pl), _ptr(worklist),
-                                              _ptr(worklist_host), ctypes.byref(shape), ctypes.c_float(scale),
-                                              _ptr(out), _ptr(lse), _stream_ptr(stream)))
+    _check_token_scales(shape, q_descale_tok, k_descale_tok, v_descale_tok)
+    _fwd_fp8(_lib.varlen_attn_fwd_fp8_blockwise, q8, k8, v8, q_descale_tok, k_descale_tok, v_descale_tok, _addr(cu),
+             _addr(pl), worklist, _addr(worklist_host), shape, scale, out, lse, stream)
+
+
+_upload_streams = {}  # device -> the stream work lists are uploaded on
+
+
+def _upload(arrays, device):
+    """Device copies of int32 record arrays, complete on return.  One copy for all of them, on a stream of its own: the
+    host waits for that copy alone and not for the kernels the caller has queued, so that the plan of the next
+    bin is made while the GPU works on this one."""
+    device = torch.device(device)
+    if device.type != "cuda":
+        return [torch.from_numpy(a).to(device) for a in arrays]
+    current = torch.cuda.current_stream(device)
+    side = _upload_streams.get(current.device)
+    if side is None:
+        side = _upload_streams.setdefault(current.device, torch.cuda.Stream(current.device))
+    rows = [len(a) for a in arrays]
+    # pinned memory comes from (and returns to) torch's caching allocator, which waits for copies still reading it
+    staging = torch.empty((sum(rows), 8), dtype=torch.int32, pin_memory=True)
+    np.concatenate(arrays, out=staging.numpy())
+    with torch.cuda.stream(side):
+        copy = staging.to(current.device, non_blocking=True)
+    copy.record_stream(current)  # freed, the memory is not reused before the caller's stream has passed its last reader
+    side.synchronize()
+    return list(copy.split(rows))
 
 
 class PackedStream:
@@ -326,14 +384,29 @@ class PackedStream:
         if max_seqlen is None:
             max_seqlen = int(lens.max()) if n else 0
         self.shape = make_shape(self.cu_seqlens[-1], n, num_q_heads, num_kv_heads, head_dim, max_seqlen, mask_mode)
-        self.worklist_host = {}
-        self.worklist = {}
-        for pid in passes:
-            wl = va_build_worklist(self.cu_seqlens, self.prefix_lens, mask_mode, pid, head_dim, num_q_heads, num_kv_heads)
-            self.worklist_host[pid] = wl
-            self.worklist[pid] = torch.from_numpy(wl).to(device)
+        self.worklist_host = {pid: va_build_worklist(self.cu_seqlens, self.prefix_lens, mask_mode, pid, head_dim,
+                                                     num_q_heads, num_kv_heads) for pid in passes}
+        self.worklist = dict(zip(self.worklist_host, _upload(list(self.worklist_host.values()), device))) if passes else {}
         self.device = device
         self._workspace = None
+        self._addrs = {}
+
+    def _host(self, a):
+        """Address of one of this object's host arrays (looking it up costs more than a kernel launch's share)."""
+        if a is None:
+            return None
+        known = self._addrs.get(id(a))
+        if known is None or known[0] is not a:
+            if len(self._addrs) > 16:
+                self._addrs.clear()
+            known = self._addrs[id(a)] = (a, a.ctypes.data)
+        return known[1]
+
+    def _bwd(self, q, k, v, out, lse, dout, scale, dq, dk, dv):
+        wl, host = self.worklist, self.worklist_host
+        return _bwd_args(q, k, v, out, lse, dout, self._host(self.cu_seqlens), self._host(self.prefix_lens),
+                         wl[VA_PASS_BWD_DKDV], self._host(host[VA_PASS_BWD_DKDV]), wl[VA_PASS_BWD_DQ],
+                         self._host(host[VA_PASS_BWD_DQ]), self.shape, scale, dq, dk, dv)
 
     def workspace(self):
         if self._workspace is None:
@@ -342,35 +415,29 @@ class PackedStream:
         return self._workspace
 
     def fwd(self, q, k, v, scale, out, lse, stream=None):
-        varlen_attn_fwd(q, k, v, self.cu_seqlens, self.prefix_lens, self.worklist[VA_PASS_FWD],
-                        self.worklist_host[VA_PASS_FWD], self.shape, scale, out, lse, stream)
+        _fwd(q, k, v, self._host(self.cu_seqlens), self._host(self.prefix_lens), self.worklist[VA_PASS_FWD],
+             self._host(self.worklist_host[VA_PASS_FWD]), self.shape, scale, out, lse, stream)
 
     def bwd(self, q, k, v, out, lse, dout, scale, dq, dk, dv, stream=None):
         ws = self.workspace()
-        varlen_attn_bwd(q, k, v, out, lse, dout, self.cu_seqlens, self.prefix_lens,
-                        self.worklist[VA_PASS_BWD_DKDV], self.worklist_host[VA_PASS_BWD_DKDV],
-                        self.worklist[VA_PASS_BWD_DQ], self.worklist_host[VA_PASS_BWD_DQ],
-                        self.shape, scale, dq, dk, dv, ws, ws.numel(), stream)
+        _check(_lib.varlen_attn_bwd(*self._bwd(q, k, v, out, lse, dout, scale, dq, dk, dv), ws.data_ptr(), ws.numel(),
+                                    _stream_ptr(stream)))
 
     def bwd_static(self, q, k, v, out, lse, dout, scale, dq, dk, dv, stream=None):
-        varlen_attn_bwd_static(q, k, v, out, lse, dout, self.cu_seqlens, self.prefix_lens,
-                               self.worklist[VA_PASS_BWD_DKDV], self.worklist_host[VA_PASS_BWD_DKDV],
-                               self.worklist[VA_PASS_BWD_DQ], self.worklist_host[VA_PASS_BWD_DQ],
-                               self.shape, scale, dq, dk, dv, stream)
+        _check(_lib.varlen_attn_bwd_static(*self._bwd(q, k, v, out, lse, dout, scale, dq, dk, dv), _stream_ptr(stream)))
 
     def bwd_stages(self, q, k, v, out, lse, dout, scale, dq, dk, dv, stages, stream=None):
         ws = self.workspace()
-        varlen_attn_bwd_stages(q, k, v, out, lse, dout, self.cu_seqlens, self.prefix_lens,
-                               self.worklist[VA_PASS_BWD_DKDV], self.worklist_host[VA_PASS_BWD_DKDV],
-                               self.worklist[VA_PASS_BWD_DQ], self.worklist_host[VA_PASS_BWD_DQ],
-                               self.shape, scale, dq, dk, dv, ws, ws.numel(), stages, stream)
+        _check(_lib.varlen_attn_bwd_stages(*self._bwd(q, k, v, out, lse, dout, scale, dq, dk, dv), ws.data_ptr(),
+                                           ws.numel(), _stream_ptr(stream), stages))
 
     def fwd_fp8_blockwise(self, q8, k8, v8, q_descale_tok, k_descale_tok, v_descale_tok, scale, out, lse, stream=None):
-        varlen_attn_fwd_fp8_blockwise(q8, k8, v8, q_descale_tok, k_descale_tok, v_descale_tok, self.cu_seqlens,
-                                      self.prefix_lens, self.worklist[VA_PASS_FWD], self.worklist_host[VA_PASS_FWD],
-                                      self.shape, scale, out, lse, stream)
+        _check_token_scales(self.shape, q_descale_tok, k_descale_tok, v_descale_tok)
+        _fwd_fp8(_lib.varlen_attn_fwd_fp8_blockwise, q8, k8, v8, q_descale_tok, k_descale_tok, v_descale_tok,
+                 self._host(self.cu_seqlens), self._host(self.prefix_lens), self.worklist[VA_PASS_FWD],
+                 self._host(self.worklist_host[VA_PASS_FWD]), self.shape, scale, out, lse, stream)
 
     def fwd_fp8(self, q8, k8, v8, q_descale, k_descale, v_descale, scale, out, lse, stream=None):
-        varlen_attn_fwd_fp8(q8, k8, v8, q_descale, k_descale, v_descale, self.cu_seqlens, self.prefix_lens,
-                            self.worklist[VA_PASS_FWD], self.worklist_host[VA_PASS_FWD], self.shape, scale,
-                            out, lse, stream)
+        _fwd_fp8(_lib.varlen_attn_fwd_fp8, q8, k8, v8, q_descale, k_descale, v_descale, self._host(self.cu_seqlens),
+                 self._host(self.prefix_lens), self.worklist[VA_PASS_FWD],
+                 self._host(self.worklist_host[VA_PASS_FWD]), self.shape, scale, out, lse, stream)
