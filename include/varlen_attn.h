@@ -255,6 +255,9 @@ int varlen_attn_fwd(const void* q, const void* k, const void* v,
  * belongs to exactly one of its works), runs first, and the dK/dV kernel reads
  * what it wrote: two kernels.  At head_dim 256 a separate pass over O and dO
  * comes first: three kernels.  No atomics; results do not depend on scheduling.
+ * Streams that leave most of the chip idle run on kernels that split a work over more workgroups (forward and
+ * backward alike; their dQ kernel computes delta at every head_dim, and one more kernel adds the parts where the
+ * steps of a key row were split): a sample's results in a small and in a large stream agree to rounding.
  *   out, lse            device in   what varlen_attn_fwd wrote
  *   dout                device in   bfloat16 [T, Hq, D]
  *   worklist_dkdv/_dq   device in   va_build_worklist(VA_PASS_BWD_DKDV / VA_PASS_BWD_DQ)

@@ -47,6 +47,32 @@ int check_shape(const va_shape* s, const int32_t* cu, const int32_t* prefix_lens
     return VA_OK;
 }
 
+// Whether a pass runs on the kernels of few_util.h: a quarter of the rows and of the serial walk per workgroup.
+//   Forward, dQ: those workgroups read four times as many tiles from L2 per row, so they pay while they fit the chip
+//   in one go: 256 CUs hold one, two or three of them at head_dim 256, 128, 64.  Measured at that line (forward,
+//   kernel us, few / persistent): 64 works of D = 256 20.6 / 33.2, 128 works 62.6 / 60.0; 128 works of D = 128
+//   28.5 / 34.1, 136 ragged ones 12.9 / 10.6; 144 works of D = 64 9.4 / 9.7, 216 works 19.4 / 18.8.
+//   dK/dV: works differ by the length of the walk over the query tiles, and the kernel of bwd_bf16.hip ends with its
+//   longest.  Here the total counts instead, at about 1 / ratio of the longest: 10.6 steps per slot, longest 54,
+//   D = 128 44 / 60 us, 24 per slot 80 / 68; D = 256, 83 per slot, longest 256, 306 / 505.  (Two steps of
+//   fixed cost per work: thousands of tiny works stay where they are.)
+bool few_works(int32_t pass, int32_t head_dim, int64_t works, int64_t steps, int64_t heaviest) {
+    const int32_t D = tile_geometry(head_dim);
+    if (pass == VA_PASS_FWD) return works <= (D == 256 ? 64 : D == 128 ? 128 : 160);
+    if (pass == VA_PASS_BWD_DQ) return works <= 128;
+    const int64_t ratio = D == 256 ? 50 : D == 128 ? 36 : 45;
+    return 100 * (steps + kWorkFixedCost * works) < ratio * (heaviest + kWorkFixedCost) * persistent_workgroups(pass, head_dim);
+}
+
+// Splits of the dK/dV pass on those kernels: with few works of very many steps (one KV head serving eight query heads,
+// D = 256: one sample of 1005 tokens is 32 workgroups of 64 steps per wave) up to one workgroup per slot of the chip, as
+// far as the workspace holds their sums and `most` pieces; and only where it takes 12 steps off each wave, since
+// the merge kernel costs about 5 us (13 steps per wave, D = 128: 26 us whole, 28 in two; 64, D = 256: 214 whole, 41 in eight).
+int32_t few_splits(int32_t head_dim, int64_t items, int64_t works, int64_t blocks, int32_t most) {
+    const int64_t s = std::min<int64_t>(most / items, persistent_workgroups(VA_PASS_BWD_DKDV, head_dim) / (4 * works));
+    return s > 1 && blocks * (s - 1) >= 12 * 4 * s ? (int32_t)s : 1;
+}
+
 // The host copy of a work list is checked against the stream it claims to
 // describe: headers, every item must lie inside one sample of cu_seqlens, and
 // the workgroup table must partition the works.
@@ -81,6 +107,7 @@ int check_worklist(const void* dev, const void* host, const va_shape* s, const i
     int32_t piece_first[kMaxPartialSlots], piece_count[kMaxPartialSlots], piece_row0[kMaxPartialSlots];
     for (int32_t i = 0; i < kMaxPartialSlots; ++i) piece_row0[i] = -1;
     int32_t num_pieces = 0;
+    int64_t steps = 0, heaviest = 0;  // inner-loop steps of all works, and of the heaviest
     for (int32_t i = 0; i < n; ++i) {
         const int32_t* it = w[lay.item_rec + i].w;
         const int32_t row0 = it[0], seq0 = it[2], L = it[7];
@@ -127,6 +154,10 @@ int check_worklist(const void* dev, const void* host, const va_shape* s, const i
             if (it[5] != (kv_len + cols - 1) / cols || it[4] < 0 || it[4] > visible(r0, L, Pm, P2m, s->mask_mode) / cols)
                 return fail(VA_EINVAL, "%s: work item %d has a bad key range", who, i);
         }
+        const int64_t work = pass == VA_PASS_BWD_DKDV ? (int64_t)it[4] * (s->num_q_heads / s->num_kv_heads)
+                                                      : it[5] - first_visible(row0 - seq0, Pm, s->mask_mode) / cols;
+        steps += work * lay.works_per_item;
+        heaviest = std::max(heaviest, work);
     }
     // Merge records: the pieces of a tile occupy consecutive slots, follow each other without gap or overlap from
     // the tile's first query tile to its last, and share the tile's first key row; every piece belongs to one.
@@ -184,6 +215,9 @@ int check_worklist(const void* dev, const void* host, const va_shape* s, const i
     if (at != lay.num_works) return fail(VA_EINVAL, "%s: workgroup table does not partition the works", who);
     *layout = lay;
     layout->flags = h1[3];
+    layout->few = few_works(pass, s->head_dim, lay.num_works, steps, heaviest) && num_merges == 0;
+    if (pass == VA_PASS_BWD_DKDV && layout->few && n > 0)
+        layout->few_splits = few_splits(s->head_dim, n, lay.num_works, heaviest * cols / 32, max_slots);
     return VA_OK;
 }
 
@@ -197,6 +231,7 @@ void set_worklist(AttnParams* p, const void* dev, const WorklistLayout& lay) {
     p->works_per_item = lay.works_per_item;
     p->merges = recs + lay.merge_rec;
     p->num_merges = lay.num_merges;
+    p->few_splits = lay.few_splits;
     p->dkdv_by_ids = (lay.flags & kListFlagInStep) ? 1 : 0;
 }
 
@@ -258,7 +293,8 @@ int varlen_attn_fwd(const void* q, const void* k, const void* v,
     p.out = out;
     p.lse = lse;
     set_worklist(&p, worklist, lay);
-    hipError_t e = launch_fwd_bf16(p, static_cast<hipStream_t>(stream));
+    const hipError_t e = lay.few ? launch_fwd_few(p, static_cast<hipStream_t>(stream))
+                                 : launch_fwd_bf16(p, static_cast<hipStream_t>(stream));
     if (e != hipSuccess) return fail(VA_EHIP, "%s: launch failed: %s", who, hipGetErrorString(e));
     return VA_OK;
 }
@@ -310,21 +346,19 @@ static int prepare_bwd(const char* who, const void* q, const void* k, const void
 static hipError_t launch_backward(AttnParams* p, hipStream_t st, const void* worklist_dkdv, const WorklistLayout& lay_dkdv,
                                   const void* worklist_dq, const WorklistLayout& lay_dq, uint32_t stages) {
     hipError_t e = hipSuccess;
-    const bool fused = dq_computes_delta(p->D);
+    const bool fused = dq_computes_delta(p->D) || lay_dq.few;
     const bool dq_first = fused && (stages & VA_BWD_STAGE_DQ);
-    if ((stages & VA_BWD_STAGE_DELTA) && !dq_first) e = launch_bwd_delta(*p, st);
-    if (e == hipSuccess && dq_first) {
+    auto launch_dq = [&] {
         set_worklist(p, worklist_dq, lay_dq);
-        e = launch_bwd_dq(*p, st);
-    }
+        return lay_dq.few ? launch_bwd_dq_few(*p, st) : launch_bwd_dq(*p, st);
+    };
+    if ((stages & VA_BWD_STAGE_DELTA) && !dq_first) e = launch_bwd_delta(*p, st);
+    if (e == hipSuccess && dq_first) e = launch_dq();
     if (e == hipSuccess && (stages & VA_BWD_STAGE_DKDV)) {
         set_worklist(p, worklist_dkdv, lay_dkdv);
-        e = launch_bwd_dkdv(*p, st);
+        e = lay_dkdv.few ? launch_bwd_dkdv_few(*p, st) : launch_bwd_dkdv(*p, st);
     }
-    if (e == hipSuccess && (stages & VA_BWD_STAGE_DQ) && !dq_first) {
-        set_worklist(p, worklist_dq, lay_dq);
-        e = launch_bwd_dq(*p, st);
-    }
+    if (e == hipSuccess && (stages & VA_BWD_STAGE_DQ) && !dq_first) e = launch_dq();
     return e;
 }
 

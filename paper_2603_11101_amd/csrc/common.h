@@ -41,6 +41,8 @@ struct WorklistLayout {
     int32_t item_rec, table_rec, id_rec, total_recs;
     int32_t num_merges, merge_rec;
     int32_t flags;  // of the list at hand (filled when a list is checked)
+    bool few;       // few enough works for the kernels of few_util.h (likewise)
+    int32_t few_splits;
 };
 
 // Tile geometry.  A forward / dQ workgroup owns kFwdBlockRows rows of the

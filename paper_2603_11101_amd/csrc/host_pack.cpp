@@ -71,6 +71,8 @@ WorklistLayout worklist_layout(int32_t pass, int32_t D, int32_t Hq, int32_t Hkv,
     l.id_rec = l.table_rec + l.num_workgroups * (kTableWordsPerWorkgroup / 8);
     l.num_merges = num_merges;
     l.flags = 0;
+    l.few = false;
+    l.few_splits = 1;
     l.merge_rec = l.id_rec + (l.num_works + 7) / 8;
     l.total_recs = l.merge_rec + num_merges;
     return l;

@@ -30,6 +30,7 @@ struct AttnParams {
     const WorkItem* merges;    // device: merge records of a dK/dV list (split key tiles)
     float* partials;           // partial-sum slots of split key tiles, in the backward workspace
     int32_t num_merges;
+    int32_t few_splits;        // workgroups that share the steps of 32 key rows (launch_bwd_dkdv_few)
     int32_t dkdv_by_ids;       // dK/dV list: workgroup b runs the work at position b of the id array
     int32_t num_items;
     int32_t num_workgroups;
@@ -69,6 +70,10 @@ hipError_t launch_fwd_fp8(const AttnParams& p, bool blockwise, hipStream_t strea
 hipError_t launch_bwd_delta(const AttnParams& p, hipStream_t stream);
 hipError_t launch_bwd_dkdv(const AttnParams& p, hipStream_t stream);
 hipError_t launch_bwd_dq(const AttnParams& p, hipStream_t stream);
+// the same passes for streams of few works (few_util.h); launch_bwd_dq_few computes delta at every head dimension
+hipError_t launch_fwd_few(const AttnParams& p, hipStream_t stream);
+hipError_t launch_bwd_dkdv_few(const AttnParams& p, hipStream_t stream);
+hipError_t launch_bwd_dq_few(const AttnParams& p, hipStream_t stream);
 hipError_t launch_quantize_e4m3(const void* x, int32_t T, int32_t H, int32_t D, void* codes, float* descale,
                                 hipStream_t stream);
 hipError_t launch_quantize_e4m3_blockwise(const void* x, const int32_t* cu_device, int32_t num_seqs, int32_t T,

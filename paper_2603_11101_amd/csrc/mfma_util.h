@@ -298,17 +298,20 @@ struct AsyncTile {
     // must lie inside the buffer: the range check compares the per-lane offset with the buffer size minus
     // the scalar offset in unsigned arithmetic, so rows past the end are only caught through the per-lane part
     VA_DEV void issue(i32x4 rsrc, unsigned tile_lds, int soffset) const {
-        int v = voff0;
-        asm volatile("" : "+v"(v));  // derive the offsets here instead of keeping PER_WAVE of them in registers
 #pragma unroll
-        for (int j = 0; j < PER_WAVE; ++j) {
-            if constexpr (DR == D) {
-                buffer_load_lds_16(tile_lds + (first + j) * 1024, (v ^ (swizzle<D>(j * RPI) << 4)) + j * row_step, rsrc, soffset);
-            } else {
-                const int c = chunk0 ^ swizzle<D>(j * RPI);
-                const int off = c < DR / 8 ? v + j * row_step + (c << 4) : 0x7ffffff0;
-                buffer_load_lds_16(tile_lds + (first + j) * 1024, off, rsrc, soffset);
-            }
+        for (int j = 0; j < PER_WAVE; ++j) issue_one(j, rsrc, tile_lds, soffset);
+    }
+    // Instruction j of PER_WAVE, for kernels that spread them over other work: the memory pipe takes one every 16
+    // cycles of a CU, and a wave that has several to issue stands still meanwhile.
+    VA_DEV void issue_one(int j, i32x4 rsrc, unsigned tile_lds, int soffset) const {
+        int v = voff0;
+        asm volatile("" : "+v"(v));  // derive the offset here instead of keeping PER_WAVE of them in registers
+        if constexpr (DR == D) {
+            buffer_load_lds_16(tile_lds + (first + j) * 1024, (v ^ (swizzle<D>(j * RPI) << 4)) + j * row_step, rsrc, soffset);
+        } else {
+            const int c = chunk0 ^ swizzle<D>(j * RPI);
+            const int off = c < DR / 8 ? v + j * row_step + (c << 4) : 0x7ffffff0;
+            buffer_load_lds_16(tile_lds + (first + j) * 1024, off, rsrc, soffset);
         }
     }
 };
