@@ -232,13 +232,20 @@ __global__ __launch_bounds__(256, D <= 128 ? 2 : 1) void bwd_dkdv_kernel(AttnPar
         src.head = w.g * G + src.in_group;
         head_buffers(w, src);
         const int qt = src.qt;
-        const unsigned st = smem_lds + st_index * STAGE_BYTES;
         const int q0 = (w.qt_first + qt) * BMQ;
-        loader.issue(src.q, st, q0 * q_row_bytes);
+        loader.issue(src.q, smem_lds + st_index * STAGE_BYTES, q0 * q_row_bytes);
+        return q0;
+    };
+    // The rest of that stage, dO and the statistics.  At D = 256 behind the first products of the step that runs
+    // meanwhile: the memory pipe takes a KiB every 16 cycles, a wave with 32 KiB to issue stands still, and there is
+    // no second wave on the SIMD (535 -> 526 us on 32k tokens, 8 / 1 heads).  At D <= 128 the second one fills that
+    // gap, and the registers the delay costs are worth more (771 -> 781 us on 64k tokens).
+    constexpr bool DELAY = D == 256 && !WINDOW;  // (nor has the window kernel registers for it)
+    auto issue_rest = [&](const StageSource& src, int st_index, int q0) {
+        const unsigned st = smem_lds + st_index * STAGE_BYTES;
         loader.issue(src.dout, st + TILE_BYTES, q0 * q_row_bytes);
         if (wave < 2)  // 64 floats each: lane i fetches row q0 + i
             buffer_load_lds_4(st + 2 * TILE_BYTES + wave * 256, lane * 4, src.aux, q0 * 4);
-        return q0;
     };
     auto issue_v = [&](const DkdvWork& w) {
         if (V_IN_LDS) {
@@ -276,6 +283,7 @@ __global__ __launch_bounds__(256, D <= 128 ? 2 : 1) void bwd_dkdv_kernel(AttnPar
     src.head = cur.g * G;
     head_buffers(cur, src);
     int q0_next = issue_next_stage(cur, src, 0);  // first query row of the stage in flight
+    issue_rest(src, 0, q0_next);
     issue_v(cur);
     load_k(cur);
 
@@ -309,11 +317,15 @@ __global__ __launch_bounds__(256, D <= 128 ? 2 : 1) void bwd_dkdv_kernel(AttnPar
         auto step = [&](const int n, auto last_tag) {
             constexpr bool last = decltype(last_tag)::value;
             const int q0 = q0_next;
-            if constexpr (!last) q0_next = issue_next_stage(cur, src, stage ^ 1);
+            if constexpr (!last) {
+                q0_next = issue_next_stage(cur, src, stage ^ 1);
+                if (!DELAY) issue_rest(src, stage ^ 1, q0_next);
+            }
             const int q_tile = stage * STAGE_BYTES;  // byte offsets of this stage's tiles
             const int do_tile = q_tile + TILE_BYTES;
             const float* lse_s = reinterpret_cast<const float*>(smem + q_tile + 2 * TILE_BYTES);
             const float* delta_s = lse_s + 64;
+            bool rest_issued = last || !DELAY;
 #pragma unroll
             for (int qb = 0; qb < QB; ++qb) {
                 const int i0 = q0 + 32 * qb;  // first query row of the block (local index in the sample)
@@ -371,6 +383,10 @@ __global__ __launch_bounds__(256, D <= 128 ? 2 : 1) void bwd_dkdv_kernel(AttnPar
                             else __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
                         }
                     }
+                }
+                if (!rest_issued) {
+                    issue_rest(src, stage ^ 1, q0_next);
+                    rest_issued = true;
                 }
                 // first transposed fragments on their way while the elementwise part runs.
                 // Step i of the last products: which = i % NW (dV from dO^T, dK from Q^T), block (i / NW) % DT,
@@ -446,6 +462,7 @@ __global__ __launch_bounds__(256, D <= 128 ? 2 : 1) void bwd_dkdv_kernel(AttnPar
                     if (i + PF < NT) __builtin_amdgcn_sched_group_barrier(0x100, 2, 1);
                 }
             }
+            if (!rest_issued) issue_rest(src, stage ^ 1, q0_next);  // no block of this step was visible to the wave
             stage ^= 1;
             if constexpr (!last) {
                 wait_async_loads();

@@ -187,16 +187,9 @@ __global__ __launch_bounds__(256, D <= 128 ? 2 : 1) void bwd_dq_kernel(AttnParam
             const int j0 = kt * BN;
             const int k_tile = stage * 2 * TILE_BYTES;
             const int v_tile = k_tile + TILE_BYTES;
-            {
-                const unsigned nk = smem_lds + (stage ^ 1) * 2 * TILE_BYTES;
-                if constexpr (!last) {
-                    loader.issue(k_rsrc, nk, (kt + 1) * tile_step);
-                    loader.issue(v_rsrc, nk + TILE_BYTES, (kt + 1) * tile_step);
-                } else if (has_next) {
-                    loader.issue(kv_rsrc(p.k, nxt), nk, first_tile(nxt) * tile_step);
-                    loader.issue(kv_rsrc(p.v, nxt), nk + TILE_BYTES, first_tile(nxt) * tile_step);
-                }
-            }
+            const unsigned nk = smem_lds + (stage ^ 1) * 2 * TILE_BYTES;
+            if constexpr (!last) loader.issue(k_rsrc, nk, (kt + 1) * tile_step);
+            else if (has_next) loader.issue(kv_rsrc(p.k, nxt), nk, first_tile(nxt) * tile_step);
             // One 32-key block at a time: S^T and dP^T (rows = key rows in registers, columns = query rows in
             // lanes), the elementwise part, then dQ^T += K^T dS^T for these 32 keys.  MFMAs alternate between
             // independent accumulators so that none waits on the one just issued.
@@ -235,6 +228,11 @@ __global__ __launch_bounds__(256, D <= 128 ? 2 : 1) void bwd_dq_kernel(AttnParam
                         __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
                         if (i + PF < NS) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
                     }
+                }
+                if (b == 0) {
+                    // V behind the first products, as in fwd_bf16.hip
+                    if constexpr (!last) loader.issue(v_rsrc, nk + TILE_BYTES, (kt + 1) * tile_step);
+                    else if (has_next) loader.issue(kv_rsrc(p.v, nxt), nk + TILE_BYTES, first_tile(nxt) * tile_step);
                 }
                 if (b == 1) {
                     // the row fragments are free now: those of the next work can start loading

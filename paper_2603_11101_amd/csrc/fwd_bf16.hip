@@ -147,17 +147,10 @@ __global__ __launch_bounds__(256, D <= 128 ? 2 : 1) void fwd_bf16_kernel(AttnPar
             const int j0 = kt * BN;
             const int k_tile = stage * 2 * TILE_BYTES;  // byte offsets of this stage's tiles
             const int v_tile = k_tile + TILE_BYTES;
-            {
-                // next tile of this work, or the first tile of the next work, into the other stage
-                const unsigned nk = smem_lds + (stage ^ 1) * 2 * TILE_BYTES;
-                if constexpr (!last) {
-                    loader.issue(k_rsrc, nk, (kt + 1) * tile_step);
-                    loader.issue(v_rsrc, nk + TILE_BYTES, (kt + 1) * tile_step);
-                } else if (has_next) {
-                    loader.issue(kv_rsrc(p.k, nxt), nk, first_tile(nxt) * tile_step);
-                    loader.issue(kv_rsrc(p.v, nxt), nk + TILE_BYTES, first_tile(nxt) * tile_step);
-                }
-            }
+            // next tile of this work, or the first tile of the next work, into the other stage
+            const unsigned nk = smem_lds + (stage ^ 1) * 2 * TILE_BYTES;
+            if constexpr (!last) loader.issue(k_rsrc, nk, (kt + 1) * tile_step);
+            else if (has_next) loader.issue(kv_rsrc(p.k, nxt), nk, first_tile(nxt) * tile_step);
 
             // S^T: two blocks of 32 keys x 32 query rows.  The K fragments are fetched from LDS kPrefetch
             // steps ahead of the MFMA that consumes them; consecutive MFMAs alternate between the two
@@ -187,6 +180,9 @@ __global__ __launch_bounds__(256, D <= 128 ? 2 : 1) void fwd_bf16_kernel(AttnPar
                     if (i + kPrefetch < NS) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
                 }
             }
+            // V behind the scores: the memory pipe takes a KiB every 16 cycles, and a wave with more to issue stands still
+            if constexpr (!last) loader.issue(v_rsrc, nk + TILE_BYTES, (kt + 1) * tile_step);
+            else if (has_next) loader.issue(kv_rsrc(p.v, nxt), nk + TILE_BYTES, first_tile(nxt) * tile_step);
             // the Q fragments are free now: those of the next work can start loading
             if constexpr (last) {
                 if (has_next) load_q(qf, nxt);

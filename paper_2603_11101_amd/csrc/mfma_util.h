@@ -225,6 +225,23 @@ VA_DEV void buffer_load_lds_16(unsigned lds_dst, int voffset, i32x4 rsrc, int so
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
                  :: "s"(lds_dst), "v"(voffset), "s"(rsrc), "s"(soffset) : "memory");
 }
+// N of them for consecutive KiB of LDS; off[i] is the per-lane offset less 1024 i
+template <int N>
+VA_DEV void buffer_load_lds_16_run(unsigned lds_dst, const int (&off)[N], i32x4 rsrc, int soffset) {
+    static_assert(N == 2 || N == 4, "");
+    lds_dst = __builtin_amdgcn_readfirstlane(lds_dst);
+    soffset = __builtin_amdgcn_readfirstlane(soffset);
+    if constexpr (N == 4)
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %5, %6 offen lds\n\t"
+                     "buffer_load_dwordx4 %2, %5, %6 offen offset:1024 lds\n\t"
+                     "buffer_load_dwordx4 %3, %5, %6 offen offset:2048 lds\n\t"
+                     "buffer_load_dwordx4 %4, %5, %6 offen offset:3072 lds"
+                     :: "s"(lds_dst), "v"(off[0]), "v"(off[1]), "v"(off[2]), "v"(off[3]), "s"(rsrc), "s"(soffset) : "memory");
+    else
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %3, %4 offen lds\n\t"
+                     "buffer_load_dwordx4 %2, %3, %4 offen offset:1024 lds"
+                     :: "s"(lds_dst), "v"(off[0]), "v"(off[1]), "s"(rsrc), "s"(soffset) : "memory");
+}
 VA_DEV void buffer_load_lds_4(unsigned lds_dst, int voffset, i32x4 rsrc, int soffset) {
     lds_dst = __builtin_amdgcn_readfirstlane(lds_dst);
     soffset = __builtin_amdgcn_readfirstlane(soffset);
@@ -298,21 +315,33 @@ struct AsyncTile {
     // must lie inside the buffer: the range check compares the per-lane offset with the buffer size minus
     // the scalar offset in unsigned arithmetic, so rows past the end are only caught through the per-lane part
     VA_DEV void issue(i32x4 rsrc, unsigned tile_lds, int soffset) const {
+        const unsigned lds = tile_lds + first * 1024;
+        if constexpr (DR == D && PER_WAVE % 2 == 0) {
+            // Up to four instructions share M0: the instruction's own offset moves both the LDS address and the memory
+            // address (measured), so it is taken off the per-lane offset again, which stays >= 0 because RPI rows of
+            // the tensor are at least the 1024 bytes an instruction fills.  One vector and one memory instruction
+            // each, where M0, a wait state and two more per load were six.
+            constexpr int N = PER_WAVE % 4 == 0 ? 4 : 2;
 #pragma unroll
-        for (int j = 0; j < PER_WAVE; ++j) issue_one(j, rsrc, tile_lds, soffset);
-    }
-    // Instruction j of PER_WAVE, for kernels that spread them over other work: the memory pipe takes one every 16
-    // cycles of a CU, and a wave that has several to issue stands still meanwhile.
-    VA_DEV void issue_one(int j, i32x4 rsrc, unsigned tile_lds, int soffset) const {
-        int v = voff0;
-        asm volatile("" : "+v"(v));  // derive the offset here instead of keeping PER_WAVE of them in registers
-        if constexpr (DR == D) {
-            buffer_load_lds_16(tile_lds + (first + j) * 1024, (v ^ (swizzle<D>(j * RPI) << 4)) + j * row_step, rsrc, soffset);
+            for (int j = 0; j < PER_WAVE; j += N) {
+                int off[N];
+#pragma unroll
+                for (int i = 0; i < N; ++i) off[i] = lane_offset(j + i) - i * 1024;
+                buffer_load_lds_16_run(lds + j * 1024, off, rsrc, soffset);
+            }
         } else {
-            const int c = chunk0 ^ swizzle<D>(j * RPI);
-            const int off = c < DR / 8 ? v + j * row_step + (c << 4) : 0x7ffffff0;
-            buffer_load_lds_16(tile_lds + (first + j) * 1024, off, rsrc, soffset);
+#pragma unroll
+            for (int j = 0; j < PER_WAVE; ++j) buffer_load_lds_16(lds + j * 1024, lane_offset(j), rsrc, soffset);
         }
+    }
+    // offset of the lane's chunk in instruction j; derived where it is used instead of keeping PER_WAVE of them in
+    // registers (the row step is made opaque, not the lane's constant: that costs no copy)
+    VA_DEV int lane_offset(int j) const {
+        int step = j * row_step;
+        if (j > 0) asm volatile("" : "+s"(step));
+        if constexpr (DR == D) return (voff0 ^ (swizzle<D>(j * RPI) << 4)) + step;
+        const int c = chunk0 ^ swizzle<D>(j * RPI);
+        return c < DR / 8 ? voff0 + step + (c << 4) : 0x7ffffff0;
     }
 };
 
