@@ -172,12 +172,10 @@ VA_DEV void add_partial(const float* slot, int which, int wave, int lane, bool f
 //          (256 registers per lane, in the accumulation registers) at D = 256
 //   DR     head dimension of the tensors in memory (a multiple of 16, D / 2 < DR <= D); D is then the
 //          geometry of the LDS tiles and register blocks only
-// FAMILY selects the mask code: 0 the masks with one boundary, 1 the three-block mask, 2 the sliding window
-// (the P word of the work holds the width W; query rows past the window of a key block skip it, and
-// blocks cut by the window's lower edge carry the mask like the diagonal ones).
-template <int D, bool V_LDS, int FAMILY, int DR>
+// The mask is a range of query rows per key (MaskBounds): a block of 32 rows is skipped where no key of the wave is
+// seen, and carries the mask where some pair of it is hidden.
+template <int D, bool V_LDS, int DR>
 __global__ __launch_bounds__(256, D <= 128 ? 2 : 1) void bwd_dkdv_kernel(AttnParams p) {
-    constexpr bool THREE = FAMILY == 1, WINDOW = FAMILY == 2;
     static_assert(DR % 16 == 0 && DR <= D && DR > D / 2, "head dimension and geometry do not match");
     constexpr bool V_IN_LDS = V_LDS, V_REGS = !V_LDS;
     constexpr int BMQ = dkdv_q_tile(D);  // query rows staged per step
@@ -205,19 +203,21 @@ __global__ __launch_bounds__(256, D <= 128 ? 2 : 1) void bwd_dkdv_kernel(AttnPar
     loader.init(wave, lane, q_row_bytes);
     const FragAddr<D> fa(lane);
 
-    // Step n of a work is query tile qt_first + qt_count - 1 - n / G of head g * G + n % G.  Q and dO rows
-    // of (sample, head) and the LSE / delta rows are raw buffers: anything past the sample reads as zero.
+    // Step n of a work is query tile qt_first + qt_count - 1 - n / G of head g * G + n % G.  One raw buffer over the rows of
+    // the sample serves all heads of the group: a head is an offset inside the row, and a row past the sample lies past the
+    // end of the buffer for every head.  (Rebuilding the buffers of the head at every step was half of the 106
+    // scalar instructions of a step; 763 -> 744 us on 64k tokens, D = 128; 515 -> 500 us at D = 256.)
     struct StageSource {
-        i32x4 q, dout, aux;  // aux: LSE rows for wave 0, delta rows for wave 1
+        i32x4 q, dout;
+        const float* stats;  // rows of the group's first head: LSE for wave 0, delta for the others
         int qt, in_group;    // query tile (from qt_first) and head inside the group of the stage issued last
-        int head;
     };
-    auto head_buffers = [&](const DkdvWork& w, StageSource& src) {
-        const size_t off = ((size_t)w.seq_row0 * p.Hq + src.head) * DR;
-        const unsigned q_bytes = (unsigned)(w.L - 1) * q_row_bytes + DR * 2;
+    auto sample_buffers = [&](const DkdvWork& w, StageSource& src) {
+        const size_t off = ((size_t)w.seq_row0 * p.Hq + w.g * G) * DR;
+        const unsigned q_bytes = (unsigned)(w.L - 1) * q_row_bytes + G * DR * 2;
         src.q = make_rsrc(static_cast<const __bf16*>(p.q) + off, q_bytes);
         src.dout = make_rsrc(static_cast<const __bf16*>(p.dout) + off, q_bytes);
-        src.aux = make_rsrc((wave == 0 ? p.lse2 : p.delta) + (size_t)src.head * p.T + w.seq_row0, (unsigned)w.L * 4);
+        src.stats = (wave == 0 ? p.lse2 : p.delta) + (size_t)(w.g * G) * p.T + w.seq_row0;
     };
     // issues the stage after the one issued last (the first call issues step 0); returns its first query row
     auto issue_next_stage = [&](const DkdvWork& w, StageSource& src, int st_index) {
@@ -229,23 +229,21 @@ __global__ __launch_bounds__(256, D <= 128 ? 2 : 1) void bwd_dkdv_kernel(AttnPar
             src.in_group = 0;
             --src.qt;
         }
-        src.head = w.g * G + src.in_group;
-        head_buffers(w, src);
-        const int qt = src.qt;
-        const int q0 = (w.qt_first + qt) * BMQ;
-        loader.issue(src.q, smem_lds + st_index * STAGE_BYTES, q0 * q_row_bytes);
+        const int q0 = (w.qt_first + src.qt) * BMQ;
+        loader.issue(src.q, smem_lds + st_index * STAGE_BYTES, q0 * q_row_bytes + src.in_group * (DR * 2));
         return q0;
     };
     // The rest of that stage, dO and the statistics.  At D = 256 behind the first products of the step that runs
     // meanwhile: the memory pipe takes a KiB every 16 cycles, a wave with 32 KiB to issue stands still, and there is
     // no second wave on the SIMD (535 -> 526 us on 32k tokens, 8 / 1 heads).  At D <= 128 the second one fills that
     // gap, and the registers the delay costs are worth more (771 -> 781 us on 64k tokens).
-    constexpr bool DELAY = D == 256 && !WINDOW;  // (nor has the window kernel registers for it)
-    auto issue_rest = [&](const StageSource& src, int st_index, int q0) {
+    constexpr bool DELAY = D == 256;
+    auto issue_rest = [&](const DkdvWork& w, const StageSource& src, int st_index, int q0) {
         const unsigned st = smem_lds + st_index * STAGE_BYTES;
-        loader.issue(src.dout, st + TILE_BYTES, q0 * q_row_bytes);
+        loader.issue(src.dout, st + TILE_BYTES, q0 * q_row_bytes + src.in_group * (DR * 2));
         if (wave < 2)  // 64 floats each: lane i fetches row q0 + i
-            buffer_load_lds_4(st + 2 * TILE_BYTES + wave * 256, lane * 4, src.aux, q0 * 4);
+            buffer_load_lds_4(st + 2 * TILE_BYTES + wave * 256, lane * 4,
+                              make_rsrc(src.stats + (size_t)src.in_group * p.T, (unsigned)w.L * 4), q0 * 4);
     };
     auto issue_v = [&](const DkdvWork& w) {
         if (V_IN_LDS) {
@@ -280,22 +278,22 @@ __global__ __launch_bounds__(256, D <= 128 ? 2 : 1) void bwd_dkdv_kernel(AttnPar
     StageSource src;
     src.in_group = G - 1;  // the first stage wraps to head 0 of the last query tile
     src.qt = cur.qt_count;
-    src.head = cur.g * G;
-    head_buffers(cur, src);
+    sample_buffers(cur, src);
     int q0_next = issue_next_stage(cur, src, 0);  // first query row of the stage in flight
-    issue_rest(src, 0, q0_next);
+    issue_rest(cur, src, 0, q0_next);
     issue_v(cur);
     load_k(cur);
 
     {
         const int n_steps = G * cur.qt_count;
-        const RowMask mask(cur.P, cur.P2, cur.L, p.mask_mode);
         const int L = cur.L;
-        // keys local query row i sees: [lo_of(i), vis_of(i))
-        auto vis_of = [&](int i) { return WINDOW ? i + 1 : mask.vis<THREE>(i); };
-        auto lo_of = [&](int i) { return WINDOW ? max(0, i + 1 - cur.P) : 0; };
         // this wave's 32 key rows; the lane owns key row jw + l32 (local index in the sample)
         const int jw = cur.kv_row0 - cur.seq_row0 + 32 * wave;
+        const MaskBounds mask(cur.P, cur.P2, L, p.mask_mode);
+        // rows from some_from up to some_end - 1 see one of the wave's keys, rows from all_from up to all_end - 1 all of them
+        const int last_key = min(jw + 31, L - 1);
+        const int some_from = mask.first_row(jw), some_end = mask.end_row(last_key);
+        const int all_from = mask.first_row(last_key), all_end = mask.end_row(jw);
 
         f32x16 dk[DT], dv[DT];
 #pragma unroll
@@ -319,7 +317,7 @@ __global__ __launch_bounds__(256, D <= 128 ? 2 : 1) void bwd_dkdv_kernel(AttnPar
             const int q0 = q0_next;
             if constexpr (!last) {
                 q0_next = issue_next_stage(cur, src, stage ^ 1);
-                if (!DELAY) issue_rest(src, stage ^ 1, q0_next);
+                if (!DELAY) issue_rest(cur, src, stage ^ 1, q0_next);
             }
             const int q_tile = stage * STAGE_BYTES;  // byte offsets of this stage's tiles
             const int do_tile = q_tile + TILE_BYTES;
@@ -330,11 +328,9 @@ __global__ __launch_bounds__(256, D <= 128 ? 2 : 1) void bwd_dkdv_kernel(AttnPar
             for (int qb = 0; qb < QB; ++qb) {
                 const int i0 = q0 + 32 * qb;  // first query row of the block (local index in the sample)
                 if (i0 >= L) break;
-                const int i1 = min(i0 + 31, L - 1);
-                if (vis_of(i1) <= jw) continue;  // nothing of this key block is visible
-                if (WINDOW && lo_of(i0) >= jw + 32) continue;  // the window of every row has moved past it
+                if (i0 + 31 < some_from || i0 >= some_end) continue;  // no pair of this block is visible
                 // rows past the sample read as zeros and must get p = 0: they count as seeing no key
-                const bool need_mask = vis_of(i0) < jw + 32 || i0 + 32 > L || (WINDOW && lo_of(i1) > jw);
+                const bool need_mask = i0 < all_from || i0 + 31 >= all_end;
 
                 // S = Q K^T and dP = dO V^T: rows = query rows (registers), columns = key rows (lanes).
                 // MFMAs alternate between the two accumulators so that none waits on the one just issued.
@@ -385,7 +381,7 @@ __global__ __launch_bounds__(256, D <= 128 ? 2 : 1) void bwd_dkdv_kernel(AttnPar
                     }
                 }
                 if (!rest_issued) {
-                    issue_rest(src, stage ^ 1, q0_next);
+                    issue_rest(cur, src, stage ^ 1, q0_next);
                     rest_issued = true;
                 }
                 // first transposed fragments on their way while the elementwise part runs.
@@ -419,23 +415,14 @@ __global__ __launch_bounds__(256, D <= 128 ? 2 : 1) void bwd_dkdv_kernel(AttnPar
                     // opaque statement ties everything below to this side of the branch.
                     int key = jw + l32;  // key row of this lane, local to the sample
                     asm volatile("" : "+v"(key));
-                    const int row_base = q0 + 32 * qb + 4 * hf;  // query row of register 0, local to the sample
+                    const int first = mask.first_row(key), base = q0 + 32 * qb + 4 * hf - first;
+                    const unsigned rows_seeing = (unsigned)max(0, mask.end_row(key) - first);
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) {
-                        const int step = 8 * (r / 4) + r % 4;  // query row of register r is row_base + step
-                        bool hidden;
-                        if constexpr (WINDOW) {
-                            // visible iff 0 <= row - key < W and the row lies inside the sample: one unsigned
-                            // comparison on a per-lane difference, one on wave-uniform values
-                            hidden = (unsigned)(row_base - key + step) >= (unsigned)cur.P || step >= L - row_base;
-                        } else {
-                            hidden = key >= mask.vis_in_sample<THREE>(row_base + step);
-                        }
-                        if (hidden) {
+                    for (int r = 0; r < 16; ++r)
+                        if ((unsigned)(base + 8 * (r / 4) + r % 4) >= rows_seeing) {
                             s[r] = 0.0f;
                             dp[r] = 0.0f;
                         }
-                    }
                 }
                 bf16x8 pb[2], dsb[2];
 #pragma unroll
@@ -462,7 +449,7 @@ __global__ __launch_bounds__(256, D <= 128 ? 2 : 1) void bwd_dkdv_kernel(AttnPar
                     if (i + PF < NT) __builtin_amdgcn_sched_group_barrier(0x100, 2, 1);
                 }
             }
-            if (!rest_issued) issue_rest(src, stage ^ 1, q0_next);  // no block of this step was visible to the wave
+            if (!rest_issued) issue_rest(cur, src, stage ^ 1, q0_next);  // no block of this step was visible to the wave
             stage ^= 1;
             if constexpr (!last) {
                 wait_async_loads();
@@ -510,23 +497,9 @@ hipError_t launch_dkdv_d(const AttnParams& p, hipStream_t stream) {
     // two stages of (Q tile, dO tile, LSE, delta), then the V tile / output staging region
     constexpr size_t smem = 2 * (2 * dkdv_q_tile(D) * D * 2 + 2 * 64 * sizeof(float)) + kDkdvKvRows * D * 2;
     const unsigned grid = (unsigned)(p.num_items * p.works_per_item);
-    // one instantiation per mask family: the masks without a second block or a lower edge do not pay for them
-    auto launch = [&](auto family) -> hipError_t {
-        constexpr int FAMILY = decltype(family)::value;
-        const hipError_t attr = VA_ALLOW_DYNAMIC_LDS((&bwd_dkdv_kernel<D, V_LDS, FAMILY, DR>), smem);
-        if (attr != hipSuccess) return attr;
-        hipLaunchKernelGGL((bwd_dkdv_kernel<D, V_LDS, FAMILY, DR>), dim3(grid), dim3(256), smem, stream, p);
-        return hipSuccess;
-    };
-    hipError_t e;
-    if (p.mask_mode == VA_MASK_THREE_BLOCK) {
-        e = launch(std::integral_constant<int, 1>{});
-    } else if (p.mask_mode == VA_MASK_SLIDING_WINDOW) {
-        e = launch(std::integral_constant<int, 2>{});
-    } else {
-        e = launch(std::integral_constant<int, 0>{});
-    }
+    hipError_t e = VA_ALLOW_DYNAMIC_LDS((&bwd_dkdv_kernel<D, V_LDS, DR>), smem);
     if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((bwd_dkdv_kernel<D, V_LDS, DR>), dim3(grid), dim3(256), smem, stream, p);
     e = hipGetLastError();
     if (e != hipSuccess || p.num_merges == 0) return e;
     constexpr size_t merge_smem = 32 * D * 2;  // one staging slice

@@ -37,7 +37,7 @@ __global__ __launch_bounds__(256, D <= 128 ? 2 : 1) void bwd_dq_few_kernel(AttnP
     if (tok0 >= tok1) return;
     const bool valid = tok < q_rows;
     const int item_row = q_row0 - seq_row0;
-    const FewMask mask(it.w[6], it.w[3], L, p.mask_mode);
+    const MaskBounds mask(it.w[6], it.w[3], L, p.mask_mode);
     const int vis = mask.vis(item_row + tok), lo = mask.lo(item_row + tok);
     const int n_tiles = (mask.vis(item_row + tok1 - 1) + kTileRows - 1) / kTileRows;
     const int full_from = (mask.lo(item_row + tok1 - 1) + kTileRows - 1) / kTileRows;  // tiles without a hidden pair
@@ -222,7 +222,7 @@ __global__ __launch_bounds__(256, D <= 128 ? 2 : 1) void bwd_dkdv_few_kernel(Att
     const int jw = it.w[0] - seq_row0 + 32 * blk.part;  // first key row of the workgroup, local to the sample
     const KeyRows<D, DR> own(p, it, blk.part, g, l32);
     if (own.keys <= 0) return;
-    const FewMask mask(it.w[6], it.w[5], L, p.mask_mode);
+    const MaskBounds mask(it.w[6], it.w[5], L, p.mask_mode);
     // query blocks of 32 rows that see one of the keys: the item's, less those that only see other parts of it
     int qb = it.w[3] * (dkdv_q_tile(D) / 32), qb_end = min((it.w[3] + it.w[4]) * (dkdv_q_tile(D) / 32), (L + 31) / 32);
     while (qb < qb_end && mask.vis(min(32 * qb + 31, L - 1)) <= jw) ++qb;

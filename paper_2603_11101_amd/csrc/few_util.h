@@ -35,23 +35,6 @@ inline int rows_log2(int rows) {  // of a power of two
     return n;
 }
 
-// The library's masks in one form without branches: local query row i sees keys lo(i) .. vis(i) - 1.
-struct FewMask {
-    RowMask upper;
-    int width;  // sliding window; beyond any row otherwise
-    VA_DEV FewMask(int P, int P2, int L, int mode)
-        : upper(mode == VA_MASK_SLIDING_WINDOW ? 0 : P, P2, L, mode), width(mode == VA_MASK_SLIDING_WINDOW ? P : 0x7fffffff) {}
-    VA_DEV int vis(int i) const { return upper.vis(i); }
-    VA_DEV int lo(int i) const { return max(0, i + 1 - width); }
-    // The rows that see key j, the other way round: first_row(j) .. end_row(j) - 1 (vis and lo never decrease).
-    VA_DEV int first_row(int j) const {
-        const int behind = upper.SF ? max(upper.P, upper.P2) : j;
-        const int second = j < upper.P2 ? upper.P : behind;
-        return j < upper.P ? 0 : second;
-    }
-    VA_DEV int end_row(int j) const { return width < upper.L ? min(upper.L, j + width) : upper.L; }
-};
-
 // A buffer of the given size, or, where there is nothing more to fetch, of none: loads through it then bring zeros
 // from nowhere, and the loop around them needs no branch (at which the compiler would move every accumulator).
 // The scalar offset of such loads must be 0: see AsyncTile::issue.

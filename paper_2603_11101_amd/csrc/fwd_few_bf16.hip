@@ -41,7 +41,7 @@ __global__ __launch_bounds__(256, D <= 128 ? 2 : 1) void fwd_few_kernel(AttnPara
     if (tok0 >= tok1) return;
     const bool valid = tok < q_rows;
     const int item_row = q_row0 - seq_row0;
-    const FewMask mask(it.w[6], it.w[3], L, p.mask_mode);
+    const MaskBounds mask(it.w[6], it.w[3], L, p.mask_mode);
     const int vis = mask.vis(item_row + tok), lo = mask.lo(item_row + tok);
     const int n_tiles = (mask.vis(item_row + tok1 - 1) + kKeys - 1) / kKeys;
     const int full_from = (mask.lo(item_row + tok1 - 1) + kKeys - 1) / kKeys;  // tiles without a hidden pair

@@ -68,19 +68,28 @@ struct RowMask {
           SF(mode == VA_MASK_PREFIX_LM || mode == VA_MASK_THREE_BLOCK ? item_L : 0),
           L(item_L) {}
     // Every arm is computed before it is chosen, so that these stay selects and never become branches.
-    // THREE = false leaves the second block out: for kernels instantiated per mask family, where the
-    // extra select per row would be paid by the masks that have no second block.
-    template <bool THREE = true>
     VA_DEV int vis(int i) const {  // any i >= 0
         const int behind = max(i + 1, SF);
-        const int second = (THREE && i < P2) ? P2 : behind;
+        const int second = i < P2 ? P2 : behind;
         return i < P ? P : second;
     }
-    template <bool THREE = true>
-    VA_DEV int vis_in_sample(int i) const {  // rows past the sample see nothing
-        const int v = vis<THREE>(i);
-        return i < L ? v : 0;
+};
+
+// Every mask, the sliding window included, seen from both sides without branches: local query row i sees the keys
+// lo(i) .. vis(i) - 1, and, since neither bound ever decreases, key j is seen by the rows first_row(j) .. end_row(j) - 1.
+struct MaskBounds {
+    RowMask upper;
+    int width;  // of the sliding window; beyond any row for the other masks
+    VA_DEV MaskBounds(int P, int P2, int L, int mode)
+        : upper(mode == VA_MASK_SLIDING_WINDOW ? 0 : P, P2, L, mode), width(mode == VA_MASK_SLIDING_WINDOW ? P : 0x7fffffff) {}
+    VA_DEV int vis(int i) const { return upper.vis(i); }
+    VA_DEV int lo(int i) const { return max(0, i + 1 - width); }
+    VA_DEV int first_row(int j) const {
+        const int behind = upper.SF ? max(upper.P, upper.P2) : j;
+        const int second = j < upper.P2 ? upper.P : behind;
+        return j < upper.P ? 0 : second;
     }
+    VA_DEV int end_row(int j) const { return width < upper.L ? min(upper.L, j + width) : upper.L; }
 };
 
 // ---------------------------------------------------------------- LDS tiles
