@@ -389,22 +389,21 @@ class PackedStream:
         self.worklist = dict(zip(self.worklist_host, _upload(list(self.worklist_host.values()), device))) if passes else {}
         self.device = device
         self._workspace = None
-        self._addrs = {}
+        self._addrs = {id(a): (a, a.ctypes.data) for a in (self.cu_seqlens, self.prefix_lens, *self.worklist_host.values())
+                       if a is not None}
 
-    def _host(self, a):
-        """Address of one of this object's host arrays (looking it up costs more than a kernel launch's share)."""
-        if a is None:
-            return None
+    def _host(self, a, prefix=False):
+        """Address of a host array: known for those made here (looking it up costs more than a kernel launch's share);
+        what a program has put in their place is converted and checked on every call."""
         known = self._addrs.get(id(a))
-        if known is None or known[0] is not a:
-            if len(self._addrs) > 16:
-                self._addrs.clear()
-            known = self._addrs[id(a)] = (a, a.ctypes.data)
-        return known[1]
+        if known is not None and known[0] is a:
+            return known[1]
+        a = _prefix(a, self.shape.mask_mode, len(self.cu_seqlens) - 1) if prefix else a if a is None else _i32(a)
+        return None if a is None else a.ctypes.data_as(ctypes.c_void_p)  # which keeps the array
 
     def _bwd(self, q, k, v, out, lse, dout, scale, dq, dk, dv):
         wl, host = self.worklist, self.worklist_host
-        return _bwd_args(q, k, v, out, lse, dout, self._host(self.cu_seqlens), self._host(self.prefix_lens),
+        return _bwd_args(q, k, v, out, lse, dout, self._host(self.cu_seqlens), self._host(self.prefix_lens, prefix=True),
                          wl[VA_PASS_BWD_DKDV], self._host(host[VA_PASS_BWD_DKDV]), wl[VA_PASS_BWD_DQ],
                          self._host(host[VA_PASS_BWD_DQ]), self.shape, scale, dq, dk, dv)
 
@@ -415,7 +414,7 @@ class PackedStream:
         return self._workspace
 
     def fwd(self, q, k, v, scale, out, lse, stream=None):
-        _fwd(q, k, v, self._host(self.cu_seqlens), self._host(self.prefix_lens), self.worklist[VA_PASS_FWD],
+        _fwd(q, k, v, self._host(self.cu_seqlens), self._host(self.prefix_lens, prefix=True), self.worklist[VA_PASS_FWD],
              self._host(self.worklist_host[VA_PASS_FWD]), self.shape, scale, out, lse, stream)
 
     def bwd(self, q, k, v, out, lse, dout, scale, dq, dk, dv, stream=None):
@@ -434,10 +433,10 @@ class PackedStream:
     def fwd_fp8_blockwise(self, q8, k8, v8, q_descale_tok, k_descale_tok, v_descale_tok, scale, out, lse, stream=None):
         _check_token_scales(self.shape, q_descale_tok, k_descale_tok, v_descale_tok)
         _fwd_fp8(_lib.varlen_attn_fwd_fp8_blockwise, q8, k8, v8, q_descale_tok, k_descale_tok, v_descale_tok,
-                 self._host(self.cu_seqlens), self._host(self.prefix_lens), self.worklist[VA_PASS_FWD],
+                 self._host(self.cu_seqlens), self._host(self.prefix_lens, prefix=True), self.worklist[VA_PASS_FWD],
                  self._host(self.worklist_host[VA_PASS_FWD]), self.shape, scale, out, lse, stream)
 
     def fwd_fp8(self, q8, k8, v8, q_descale, k_descale, v_descale, scale, out, lse, stream=None):
         _fwd_fp8(_lib.varlen_attn_fwd_fp8, q8, k8, v8, q_descale, k_descale, v_descale, self._host(self.cu_seqlens),
-                 self._host(self.prefix_lens), self.worklist[VA_PASS_FWD],
+                 self._host(self.prefix_lens, prefix=True), self.worklist[VA_PASS_FWD],
                  self._host(self.worklist_host[VA_PASS_FWD]), self.shape, scale, out, lse, stream)

@@ -601,3 +601,25 @@ def test_bench_refuses_more_than_one_gpu():
     root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
     r = subprocess.run([sys.executable, os.path.join(root, "bench.py"), "--gpus", "2"], capture_output=True, text=True)
     assert r.returncode != 0 and "one GPU" in (r.stdout + r.stderr)
+
+
+def test_packed_stream_reads_replaced_host_arrays():
+    """A program may assign other host arrays: they are converted, and prefix lengths checked, on every call."""
+    lens = [40, 17]
+    cu, pl, _ = va.va_bin_layout(np.array(lens, dtype=np.int32), np.array([20, 5], dtype=np.int32))
+    ps = va.PackedStream(cu, pl, va.VA_MASK_PREFIX_LM, 2, 1, 64, device="cpu")
+
+    def read(p, n):
+        return list(ctypes.cast(p, ctypes.POINTER(ctypes.c_int32))[:n])
+
+    assert read(ps._host(ps.cu_seqlens), 3) == [0, 40, 57] and read(ps._host(ps.prefix_lens, prefix=True), 2) == [20, 5]
+    wide = ps.cu_seqlens = np.array([0, 40, 57], dtype=np.int64)
+    assert read(ps._host(ps.cu_seqlens), 3) == [0, 40, 57]
+    wide[1] = 41  # a later write is seen
+    assert read(ps._host(ps.cu_seqlens), 3) == [0, 41, 57]
+    ps.prefix_lens = [7, 8]
+    assert read(ps._host(ps.prefix_lens, prefix=True), 2) == [7, 8]
+    ps.prefix_lens = np.array([7], dtype=np.int32)
+    with pytest.raises(ValueError):
+        ps._host(ps.prefix_lens, prefix=True)
+    assert ps._host(None, prefix=True) is None
