@@ -392,6 +392,9 @@ class PackedStream:
         self._addrs = {id(a): (a, a.ctypes.data) for a in (self.cu_seqlens, self.prefix_lens, *self.worklist_host.values())
                        if a is not None}
 
+    def __getstate__(self):
+        return dict(self.__dict__, _addrs={})  # a copy holds arrays of its own: these addresses are not theirs
+
     def _host(self, a, prefix=False):
         """Address of a host array: known for those made here (looking it up costs more than a kernel launch's share);
         what a program has put in their place is converted and checked on every call."""

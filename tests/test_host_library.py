@@ -2,8 +2,10 @@
 header declares, and its host-side integer work (first-fit packing, layout,
 work lists, E4M3 quantiser) equals the oracle's bit for bit.  Device entry
 points are only driven into their host-side validation errors here."""
+import copy
 import ctypes
 import os
+import pickle
 import re
 
 import numpy as np
@@ -623,3 +625,14 @@ def test_packed_stream_reads_replaced_host_arrays():
     with pytest.raises(ValueError):
         ps._host(ps.prefix_lens, prefix=True)
     assert ps._host(None, prefix=True) is None
+
+
+@pytest.mark.parametrize("duplicate", [copy.copy, copy.deepcopy, lambda ps: pickle.loads(pickle.dumps(ps))])
+def test_copies_of_a_packed_stream_keep_no_addresses_of_the_original(duplicate):
+    ps = va.PackedStream(np.array([0, 40, 57], dtype=np.int32), None, va.VA_MASK_CAUSAL, 2, 1, 64, device="cpu")
+    twin = duplicate(ps)
+    assert all(known is not None and known.ctypes.data == addr for known, addr in twin._addrs.values())
+    addr = twin._host(twin.cu_seqlens)
+    assert list(ctypes.cast(addr, ctypes.POINTER(ctypes.c_int32))[:3]) == [0, 40, 57]
+    assert ctypes.cast(addr, ctypes.c_void_p).value == twin.cu_seqlens.ctypes.data
+    assert set(ps._addrs) == {id(ps.cu_seqlens), *map(id, ps.worklist_host.values())}  # the original keeps its own
