@@ -350,22 +350,21 @@ _upload_streams = {}  # device -> the stream work lists are uploaded on
 def _upload(arrays, device):
     """Device copies of int32 record arrays, complete on return.  One copy for all of them, on a stream of its own: the
     host waits for that copy alone and not for the kernels the caller has queued, so that the plan of the next
-    bin is made while the GPU works on this one."""
+    bin is made while the GPU works on this one.  From pageable memory: the first pinned buffer of a size takes longer
+    than its copies save (a fresh 64k-token bin, forward and backward, 1887 us through pinned memory, 1817 without)."""
     device = torch.device(device)
     if device.type != "cuda":
         return [torch.from_numpy(a).to(device) for a in arrays]
     current = torch.cuda.current_stream(device)
+    records = torch.from_numpy(np.concatenate(arrays) if len(arrays) > 1 else arrays[0])
+    rows = [len(a) for a in arrays]
     side = _upload_streams.get(current.device)
     if side is None:
         side = _upload_streams.setdefault(current.device, torch.cuda.Stream(current.device))
-    rows = [len(a) for a in arrays]
-    # pinned memory comes from (and returns to) torch's caching allocator, which waits for copies still reading it
-    staging = torch.empty((sum(rows), 8), dtype=torch.int32, pin_memory=True)
-    np.concatenate(arrays, out=staging.numpy())
     with torch.cuda.stream(side):
-        copy = staging.to(current.device, non_blocking=True)
+        copy = records.to(current.device, non_blocking=True)
     copy.record_stream(current)  # freed, the memory is not reused before the caller's stream has passed its last reader
-    side.synchronize()
+    side.synchronize()  # the copy has read the host records too
     return list(copy.split(rows))
 
 
