@@ -73,3 +73,20 @@ def test_two_streams_from_two_threads_give_the_bits_of_sequential_calls():
     for i in range(2):
         for n in ref[i]:
             assert torch.equal(ref[i][n], bufs[i][n]), (i, n)
+
+
+def test_the_lists_of_a_plan_are_memory_of_the_callers_stream():
+    # Dropped, they are used again in the order of the stream they belong to.  A plan made on one stream, used on
+    # another and dropped before the first waits for the second is safe only if that is the stream it was made on.
+    cu = np.array([0, 70, 199], dtype=np.int32)
+    print("stream of a plan's lists", flush=True)
+    mine = torch.cuda.Stream(device=DEV)   # default priority
+    with torch.cuda.stream(mine):
+        plans = [va.PackedStream(cu, None, va.VA_MASK_CAUSAL, 4, 2, 128, device=DEV),
+                 va.PackedStream(cu, None, va.VA_MASK_CAUSAL, 4, 2, 128, device=DEV, passes=(va.VA_PASS_FWD,))]
+    for ps in plans:
+        for pid, records in ps.worklist.items():
+            owner = [seg["stream"] for seg in torch.cuda.memory_snapshot()
+                     if seg["address"] <= records.data_ptr() < seg["address"] + seg["total_size"]]
+            assert owner == [mine.cuda_stream], pid
+            assert np.array_equal(records.cpu().numpy(), ps.worklist_host[pid])
