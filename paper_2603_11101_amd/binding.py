@@ -384,18 +384,29 @@ class PackedStream:
 
     def _host(self, a, prefix=False):
         """Address of a host array: known for those made here (looking it up costs more than a kernel launch's share);
-        what a program has put in their place is converted and checked on every call."""
+        what a program has put in their place is converted on every call."""
         known = self._addrs.get(id(a))
         if known is not None and known[0] is a:
             return known[1]
         a = _prefix(a, self.shape.mask_mode, len(self.cu_seqlens) - 1) if prefix else a if a is None else _i32(a)
         return None if a is None else a.ctypes.data_as(ctypes.c_void_p)  # which keeps the array
 
+    def _rows(self):
+        """Addresses of cu_seqlens and prefix_lens.  The library cannot see how long they are, and a program may assign
+        either, or change the shape: on every call they are compared with each other and with the number of samples."""
+        cu, pl, n, mode = self.cu_seqlens, self.prefix_lens, self.shape.num_seqs, self.shape.mask_mode
+        if np.size(cu) <= n:
+            raise ValueError(f"cu_seqlens holds {np.size(cu)} entries, {n} samples need {n + 1}")
+        if pl is not None and mode != VA_MASK_CAUSAL:
+            ends = 2 if mode == VA_MASK_THREE_BLOCK else 1
+            if np.size(pl) != ends * (len(cu) - 1) or np.size(pl) < ends * n:
+                raise ValueError(f"prefix_lens holds {np.size(pl)} entries, mask mode {mode} needs {ends * (len(cu) - 1)}")
+        return self._host(cu), self._host(pl, prefix=True)
+
     def _bwd(self, q, k, v, out, lse, dout, scale, dq, dk, dv):
         wl, host = self.worklist, self.worklist_host
-        return _bwd_args(q, k, v, out, lse, dout, self._host(self.cu_seqlens), self._host(self.prefix_lens, prefix=True),
-                         wl[VA_PASS_BWD_DKDV], self._host(host[VA_PASS_BWD_DKDV]), wl[VA_PASS_BWD_DQ],
-                         self._host(host[VA_PASS_BWD_DQ]), self.shape, scale, dq, dk, dv)
+        return _bwd_args(q, k, v, out, lse, dout, *self._rows(), wl[VA_PASS_BWD_DKDV], self._host(host[VA_PASS_BWD_DKDV]),
+                         wl[VA_PASS_BWD_DQ], self._host(host[VA_PASS_BWD_DQ]), self.shape, scale, dq, dk, dv)
 
     def workspace(self):
         if self._workspace is None:
@@ -404,8 +415,8 @@ class PackedStream:
         return self._workspace
 
     def fwd(self, q, k, v, scale, out, lse, stream=None):
-        _fwd(q, k, v, self._host(self.cu_seqlens), self._host(self.prefix_lens, prefix=True), self.worklist[VA_PASS_FWD],
-             self._host(self.worklist_host[VA_PASS_FWD]), self.shape, scale, out, lse, stream)
+        _fwd(q, k, v, *self._rows(), self.worklist[VA_PASS_FWD], self._host(self.worklist_host[VA_PASS_FWD]), self.shape,
+             scale, out, lse, stream)
 
     def bwd(self, q, k, v, out, lse, dout, scale, dq, dk, dv, stream=None):
         ws = self.workspace()
@@ -423,10 +434,9 @@ class PackedStream:
     def fwd_fp8_blockwise(self, q8, k8, v8, q_descale_tok, k_descale_tok, v_descale_tok, scale, out, lse, stream=None):
         _check_token_scales(self.shape, q_descale_tok, k_descale_tok, v_descale_tok)
         _fwd_fp8(_lib.varlen_attn_fwd_fp8_blockwise, q8, k8, v8, q_descale_tok, k_descale_tok, v_descale_tok,
-                 self._host(self.cu_seqlens), self._host(self.prefix_lens, prefix=True), self.worklist[VA_PASS_FWD],
-                 self._host(self.worklist_host[VA_PASS_FWD]), self.shape, scale, out, lse, stream)
+                 *self._rows(), self.worklist[VA_PASS_FWD], self._host(self.worklist_host[VA_PASS_FWD]), self.shape, scale,
+                 out, lse, stream)
 
     def fwd_fp8(self, q8, k8, v8, q_descale, k_descale, v_descale, scale, out, lse, stream=None):
-        _fwd_fp8(_lib.varlen_attn_fwd_fp8, q8, k8, v8, q_descale, k_descale, v_descale, self._host(self.cu_seqlens),
-                 self._host(self.prefix_lens, prefix=True), self.worklist[VA_PASS_FWD],
-                 self._host(self.worklist_host[VA_PASS_FWD]), self.shape, scale, out, lse, stream)
+        _fwd_fp8(_lib.varlen_attn_fwd_fp8, q8, k8, v8, q_descale, k_descale, v_descale, *self._rows(),
+                 self.worklist[VA_PASS_FWD], self._host(self.worklist_host[VA_PASS_FWD]), self.shape, scale, out, lse, stream)

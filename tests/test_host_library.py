@@ -10,6 +10,7 @@ import re
 
 import numpy as np
 import pytest
+import torch
 
 from oracle import e4m3 as oe
 from oracle import packing as op
@@ -606,7 +607,7 @@ def test_bench_refuses_more_than_one_gpu():
 
 
 def test_packed_stream_reads_replaced_host_arrays():
-    """A program may assign other host arrays: they are converted, and prefix lengths checked, on every call."""
+    """A program may assign other host arrays: they are converted on every call."""
     lens = [40, 17]
     cu, pl, _ = va.va_bin_layout(np.array(lens, dtype=np.int32), np.array([20, 5], dtype=np.int32))
     ps = va.PackedStream(cu, pl, va.VA_MASK_PREFIX_LM, 2, 1, 64, device="cpu")
@@ -625,6 +626,51 @@ def test_packed_stream_reads_replaced_host_arrays():
     with pytest.raises(ValueError):
         ps._host(ps.prefix_lens, prefix=True)
     assert ps._host(None, prefix=True) is None
+
+
+def _calls_of(ps):
+    """Every device call of a plan, as far as the host checks: its tensors are never looked at."""
+    class Stream:
+        cuda_stream = 0
+
+    x = np.zeros(4, dtype=np.float32)
+    g = (x, x, x, x, x, x, 0.1, x, x, x)
+    T, Hq, Hkv = ps.shape.total_tokens, ps.shape.num_q_heads, ps.shape.num_kv_heads
+    tok = [np.zeros((T, h), dtype=np.float32) for h in (Hq, Hkv, Hkv)]
+    ps._workspace = torch.empty(256, dtype=torch.uint8)
+    return [lambda: ps.fwd(x, x, x, 0.1, x, x, stream=Stream), lambda: ps.bwd(*g, stream=Stream),
+            lambda: ps.bwd_static(*g, stream=Stream), lambda: ps.bwd_stages(*g, va.VA_BWD_STAGE_ALL, stream=Stream),
+            lambda: ps.fwd_fp8(x, x, x, x, x, x, 0.1, x, x, stream=Stream),
+            lambda: ps.fwd_fp8_blockwise(x, x, x, *tok, 0.1, x, x, stream=Stream)]
+
+
+def _shorter(ps):
+    ps.cu_seqlens = ps.cu_seqlens[:-1].copy()
+
+
+def _more_samples(ps):
+    ps.shape.num_seqs += 1
+
+
+def _three_block(ps):
+    ps.shape.mask_mode = va.VA_MASK_THREE_BLOCK
+
+
+def _longer(ps):  # with block ends per entry of cu_seqlens no longer
+    ps.cu_seqlens = np.append(ps.cu_seqlens, ps.cu_seqlens[-1])
+
+
+@pytest.mark.parametrize("mode,change", [(va.VA_MASK_CAUSAL, _shorter), (va.VA_MASK_CAUSAL, _more_samples)] + [
+    (m, c) for m in (va.VA_MASK_PREFIX_LM, va.VA_MASK_SLIDING_WINDOW) for c in (_shorter, _more_samples, _three_block, _longer)])
+def test_packed_stream_compares_its_host_arrays_on_every_call(mode, change):
+    """The library cannot see the lengths of cu_seqlens and prefix_lens: whatever a program assigned in the plan, no
+    call may read past either."""
+    cu, pl, _ = va.va_bin_layout(np.array([40, 17, 64], dtype=np.int32), np.array([20, 5, 3], dtype=np.int32))
+    ps = va.PackedStream(cu, None if mode == va.VA_MASK_CAUSAL else pl, mode, 2, 1, 64, device="cpu")
+    change(ps)
+    for call in _calls_of(ps):
+        with pytest.raises(ValueError):
+            call()
 
 
 @pytest.mark.parametrize("duplicate", [copy.copy, copy.deepcopy, lambda ps: pickle.loads(pickle.dumps(ps))])
