@@ -394,13 +394,14 @@ class PackedStream:
     def _rows(self):
         """Addresses of cu_seqlens and prefix_lens.  The library cannot see how long they are, and a program may assign
         either, or change the shape: on every call they are compared with each other and with the number of samples."""
-        cu, pl, n, mode = self.cu_seqlens, self.prefix_lens, self.shape.num_seqs, self.shape.mask_mode
-        if np.size(cu) <= n:
+        cu, pl, n = self.cu_seqlens, self.prefix_lens, self.shape.num_seqs
+        if len(cu) <= n and np.size(cu) <= n:
             raise ValueError(f"cu_seqlens holds {np.size(cu)} entries, {n} samples need {n + 1}")
-        if pl is not None and mode != VA_MASK_CAUSAL:
+        if pl is not None:
+            mode, entries = self.shape.mask_mode, pl.size if isinstance(pl, np.ndarray) else np.size(pl)
             ends = 2 if mode == VA_MASK_THREE_BLOCK else 1
-            if np.size(pl) != ends * (len(cu) - 1) or np.size(pl) < ends * n:
-                raise ValueError(f"prefix_lens holds {np.size(pl)} entries, mask mode {mode} needs {ends * (len(cu) - 1)}")
+            if mode != VA_MASK_CAUSAL and (entries != ends * (len(cu) - 1) or entries < ends * n):
+                raise ValueError(f"prefix_lens holds {entries} entries, mask mode {mode} needs {ends * (len(cu) - 1)}")
         return self._host(cu), self._host(pl, prefix=True)
 
     def _bwd(self, q, k, v, out, lse, dout, scale, dq, dk, dv):
