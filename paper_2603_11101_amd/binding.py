@@ -361,6 +361,8 @@ class PackedStream:
     the host index arrays, the three work lists (host copies and device copies)
     and the shape record.  Plumbing only."""
 
+    _addrs = {}  # of a plan whose saved state holds none
+
     def __init__(self, cu_seqlens, prefix_lens, mask_mode, num_q_heads, num_kv_heads, head_dim,
                  max_seqlen=None, device="cuda:0", passes=(VA_PASS_FWD, VA_PASS_BWD_DKDV, VA_PASS_BWD_DQ)):
         self.cu_seqlens = _i32(cu_seqlens)

@@ -629,11 +629,12 @@ def test_packed_stream_reads_replaced_host_arrays():
 
 
 def _calls_of(ps):
-    """Every device call of a plan, as far as the host checks: its tensors are never looked at."""
+    """Every device call of a plan, as far as the host checks: its tensors are misaligned, so nothing is launched."""
     class Stream:
         cuda_stream = 0
 
-    x = np.zeros(4, dtype=np.float32)
+    x = np.zeros(64, dtype=np.uint8)
+    x = x[1 - x.ctypes.data % 2:][:32]
     g = (x, x, x, x, x, x, 0.1, x, x, x)
     T, Hq, Hkv = ps.shape.total_tokens, ps.shape.num_q_heads, ps.shape.num_kv_heads
     tok = [np.zeros((T, h), dtype=np.float32) for h in (Hq, Hkv, Hkv)]
@@ -682,3 +683,14 @@ def test_copies_of_a_packed_stream_keep_no_addresses_of_the_original(duplicate):
     assert list(ctypes.cast(addr, ctypes.POINTER(ctypes.c_int32))[:3]) == [0, 40, 57]
     assert ctypes.cast(addr, ctypes.c_void_p).value == twin.cu_seqlens.ctypes.data
     assert set(ps._addrs) == {id(ps.cu_seqlens), *map(id, ps.worklist_host.values())}  # the original keeps its own
+
+
+def test_a_plan_saved_without_addresses_still_runs():
+    """Plans saved before addresses were remembered hold the arrays alone; calls look the addresses up."""
+    ps = va.PackedStream(np.array([0, 40, 57], dtype=np.int32), None, va.VA_MASK_CAUSAL, 2, 1, 64, device="cpu")
+    old = va.PackedStream.__new__(va.PackedStream)
+    old.__dict__.update({name: value for name, value in ps.__dict__.items() if name != "_addrs"})
+    for call in _calls_of(old):
+        with pytest.raises(va.VarlenAttnError) as e:  # cu_seqlens has been read; the tensors come next
+            call()
+        assert e.value.code in (va.VA_EALIGN, va.VA_EHIP)  # bwd_static asks for its scratch memory first
