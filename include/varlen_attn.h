@@ -291,7 +291,8 @@ int va_quantize_e4m3_per_head_device(const void* x_bf16, int32_t T, int32_t H, i
 /*
  * (This library's own, for harnesses that account for the backward kernel by kernel.)
  * Whether varlen_attn_bwd at this head_dim launches the separate delta pass
- * (1) or its dQ kernel computes delta (0); see varlen_attn_bwd.  Host only,
+ * (1) or its dQ kernel computes delta (0); see varlen_attn_bwd.  The answer is for streams that fill the chip:
+ * for those that leave most of it idle the dQ kernel computes delta at every head_dim.  Host only,
  * no error cases: any other head_dim answers 1.
  */
 int va_bwd_has_delta_kernel(int32_t head_dim);
@@ -301,9 +302,11 @@ int va_bwd_has_delta_kernel(int32_t head_dim);
  * paper names no such call).  `stages` is a non-empty combination of
  *   VA_BWD_STAGE_DELTA  delta = rowsum(dO * O) (kept negated) and LSE * log2(e) into the workspace
  *   VA_BWD_STAGE_DKDV   dK and dV; reads both arrays from the workspace
- *   VA_BWD_STAGE_DQ     dQ; at head_dim <= 128 its kernel also writes both arrays
+ *   VA_BWD_STAGE_DQ     dQ; at head_dim <= 128, and at any head_dim for streams that leave most of the chip idle,
+ *                       its kernel also writes both arrays
  *                       (VA_BWD_STAGE_DELTA is then implied and costs nothing extra)
  * in the order varlen_attn_bwd runs them; VA_BWD_STAGE_ALL is varlen_attn_bwd.
+ * Above head_dim 128 VA_BWD_STAGE_DELTA without VA_BWD_STAGE_DQ writes the bits the whole backward works with.
  * For callers that need one side only (frozen keys and values: dQ alone) and
  * for timing one kernel at a time with the caller's own events.  A call with
  * VA_BWD_STAGE_DKDV but without the stage that fills the workspace reads what

@@ -342,7 +342,8 @@ static int prepare_bwd(const char* who, const void* q, const void* k, const void
 
 // The kernels of one backward call, on one stream, restricted to `stages`.  Where the dQ kernel computes
 // delta and the rescaled LSE itself it runs first and the dK/dV kernel, which reads both, after it;
-// otherwise a pass over O and dO comes first.
+// otherwise a pass over O and dO comes first.  That pass asked for without dQ gives what the whole backward would
+// have left: for few works at head_dim > 128 it is the delta part of their dQ kernel.
 static hipError_t launch_backward(AttnParams* p, hipStream_t st, const void* worklist_dkdv, const WorklistLayout& lay_dkdv,
                                   const void* worklist_dq, const WorklistLayout& lay_dq, uint32_t stages) {
     hipError_t e = hipSuccess;
@@ -350,9 +351,16 @@ static hipError_t launch_backward(AttnParams* p, hipStream_t st, const void* wor
     const bool dq_first = fused && (stages & VA_BWD_STAGE_DQ);
     auto launch_dq = [&] {
         set_worklist(p, worklist_dq, lay_dq);
-        return lay_dq.few ? launch_bwd_dq_few(*p, st) : launch_bwd_dq(*p, st);
+        return lay_dq.few ? launch_bwd_dq_few(*p, false, st) : launch_bwd_dq(*p, st);
     };
-    if ((stages & VA_BWD_STAGE_DELTA) && !dq_first) e = launch_bwd_delta(*p, st);
+    if ((stages & VA_BWD_STAGE_DELTA) && !dq_first) {
+        if (fused && !dq_computes_delta(p->D)) {
+            set_worklist(p, worklist_dq, lay_dq);
+            e = launch_bwd_dq_few(*p, true, st);
+        } else {
+            e = launch_bwd_delta(*p, st);
+        }
+    }
     if (e == hipSuccess && dq_first) e = launch_dq();
     if (e == hipSuccess && (stages & VA_BWD_STAGE_DKDV)) {
         set_worklist(p, worklist_dkdv, lay_dkdv);

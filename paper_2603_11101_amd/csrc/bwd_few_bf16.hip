@@ -2,7 +2,8 @@
 // workgroup, their tiles shared by its four waves (see few_util.h).
 //
 // The dQ kernel computes delta = rowsum(dO * O) and LSE * log2(e) of its rows at every head dimension and leaves
-// them in the workspace, so it runs first and no separate pass over O and dO is launched.
+// them in the workspace, so it runs first and no separate pass over O and dO is launched.  (only_delta: it does that and
+// ends; for a caller who asks for delta without dQ and gets the bits of the whole backward.)
 #include "few_util.h"
 
 namespace va {
@@ -14,7 +15,7 @@ constexpr int kTileRows = 32;  // rows of a wave's tile (keys for dQ, queries fo
 constexpr int kPrefetch = 4;   // LDS fragment reads in flight ahead of the MFMA that uses them
 
 template <int D, int DR>
-__global__ __launch_bounds__(256, D <= 128 ? 2 : 1) void bwd_dq_few_kernel(AttnParams p, int bmt_log2) {
+__global__ __launch_bounds__(256, D <= 128 ? 2 : 1) void bwd_dq_few_kernel(AttnParams p, int bmt_log2, bool only_delta) {
     constexpr int KSTEPS = DR / 16;
     constexpr int DT = (DR + 31) / 32;
     constexpr int TILE = kTileRows * D * 2;
@@ -97,6 +98,10 @@ __global__ __launch_bounds__(256, D <= 128 ? 2 : 1) void bwd_dq_few_kernel(AttnP
             p.delta[stat] = -delta;  // kept negated
             p.lse2[stat] = lse2;
         }
+    }
+    if (only_delta) {
+        wait_async_loads();  // they write LDS: not after the workgroup has ended
+        return;
     }
     const FragAddr<D> fa(lane);
     const float c = p.scale * kLog2e;
@@ -426,12 +431,12 @@ __global__ __launch_bounds__(256) void bwd_dkdv_few_merge_kernel(AttnParams p, i
 }
 
 template <int D, int DR = D>
-hipError_t launch_dq_d(const AttnParams& p, hipStream_t stream) {
+hipError_t launch_dq_d(const AttnParams& p, bool only_delta, hipStream_t stream) {
     constexpr size_t smem = kFewWaves * 2 * kTileRows * D * 2;
     const hipError_t attr = VA_ALLOW_DYNAMIC_LDS((&bwd_dq_few_kernel<D, DR>), smem);
     if (attr != hipSuccess) return attr;
     hipLaunchKernelGGL((bwd_dq_few_kernel<D, DR>), dim3(few_grid(p.num_items * p.works_per_item)), dim3(256), smem, stream, p,
-                       rows_log2(kDqBlockRows / heads_per_block(p.Hq, p.Hkv)));
+                       rows_log2(kDqBlockRows / heads_per_block(p.Hq, p.Hkv)), only_delta);
     return hipGetLastError();
 }
 
@@ -451,16 +456,16 @@ hipError_t launch_dkdv_d(const AttnParams& p, hipStream_t stream) {
 
 }  // namespace
 
-hipError_t launch_bwd_dq_few(const AttnParams& p, hipStream_t stream) {
+hipError_t launch_bwd_dq_few(const AttnParams& p, bool only_delta, hipStream_t stream) {
     switch (p.D) {
-        case 48: return launch_dq_d<64, 48>(p, stream);
-        case 64: return launch_dq_d<64>(p, stream);
-        case 80: return launch_dq_d<128, 80>(p, stream);
-        case 96: return launch_dq_d<128, 96>(p, stream);
-        case 128: return launch_dq_d<128>(p, stream);
-        case 160: return launch_dq_d<256, 160>(p, stream);
-        case 192: return launch_dq_d<256, 192>(p, stream);
-        case 256: return launch_dq_d<256>(p, stream);
+        case 48: return launch_dq_d<64, 48>(p, only_delta, stream);
+        case 64: return launch_dq_d<64>(p, only_delta, stream);
+        case 80: return launch_dq_d<128, 80>(p, only_delta, stream);
+        case 96: return launch_dq_d<128, 96>(p, only_delta, stream);
+        case 128: return launch_dq_d<128>(p, only_delta, stream);
+        case 160: return launch_dq_d<256, 160>(p, only_delta, stream);
+        case 192: return launch_dq_d<256, 192>(p, only_delta, stream);
+        case 256: return launch_dq_d<256>(p, only_delta, stream);
         default: return hipErrorInvalidValue;
     }
 }

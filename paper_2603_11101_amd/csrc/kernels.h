@@ -70,10 +70,11 @@ hipError_t launch_fwd_fp8(const AttnParams& p, bool blockwise, hipStream_t strea
 hipError_t launch_bwd_delta(const AttnParams& p, hipStream_t stream);
 hipError_t launch_bwd_dkdv(const AttnParams& p, hipStream_t stream);
 hipError_t launch_bwd_dq(const AttnParams& p, hipStream_t stream);
-// the same passes for streams of few works (few_util.h); launch_bwd_dq_few computes delta at every head dimension
+// the same passes for streams of few works (few_util.h); launch_bwd_dq_few computes delta at every head dimension,
+// and nothing else if only_delta
 hipError_t launch_fwd_few(const AttnParams& p, hipStream_t stream);
 hipError_t launch_bwd_dkdv_few(const AttnParams& p, hipStream_t stream);
-hipError_t launch_bwd_dq_few(const AttnParams& p, hipStream_t stream);
+hipError_t launch_bwd_dq_few(const AttnParams& p, bool only_delta, hipStream_t stream);
 hipError_t launch_quantize_e4m3(const void* x, int32_t T, int32_t H, int32_t D, void* codes, float* descale,
                                 hipStream_t stream);
 hipError_t launch_quantize_e4m3_blockwise(const void* x, const int32_t* cu_device, int32_t num_seqs, int32_t T,

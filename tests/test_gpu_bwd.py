@@ -260,3 +260,34 @@ def test_backward_by_stages_equals_the_whole_backward(Hq, Hkv, D):
     with pytest.raises(va.VarlenAttnError) as e:
         ps.bwd_stages(tq, tk, tv, out, lse, tdo, scale, *got, 8)
     assert e.value.code == va.VA_EINVAL
+
+
+@pytest.mark.parametrize("D", [160, 256])
+@pytest.mark.parametrize("copies", [1, 12])
+def test_delta_asked_for_alone_is_the_delta_of_the_whole_backward(D, copies):
+    # Above head dimension 128, delta, dK/dV and dQ one call at a time, and the first two in one, give the bits of
+    # varlen_attn_bwd: for few works, whose dQ kernel computes delta in the whole backward, and for many
+    import torch
+    from gpu_util import DEV, to_dev_bf16
+    Hq, Hkv = 8, 1
+    lens = [70, 129, 40, 300, 1] * copies
+    cu, _, q, k, v, do = wl.random_stream(90 + D, lens, Hq, Hkv, D)
+    scale = 1.0 / np.sqrt(D)
+    print(f"delta alone D={D} samples={len(lens)}", flush=True)
+    ps = va.PackedStream(cu, None, va.VA_MASK_CAUSAL, Hq, Hkv, D, device=DEV)
+    assert (int(ps.worklist_host[va.VA_PASS_BWD_DQ][1, 1]) <= 128) == (copies == 1)  # works, and the line between the kernels
+    tq, tk, tv, tdo = (to_dev_bf16(x) for x in (q, k, v, do))
+    out, lse = torch.empty_like(tq), torch.empty((Hq, int(cu[-1])), dtype=torch.float32, device=DEV)
+    ps.fwd(tq, tk, tv, scale, out, lse)
+    want = [torch.empty_like(t) for t in (tq, tk, tv)]
+    ps.bwd(tq, tk, tv, out, lse, tdo, scale, *want)
+    torch.cuda.synchronize()
+    for order in ((va.VA_BWD_STAGE_DELTA, va.VA_BWD_STAGE_DKDV, va.VA_BWD_STAGE_DQ),
+                  (va.VA_BWD_STAGE_DELTA | va.VA_BWD_STAGE_DKDV, va.VA_BWD_STAGE_DQ)):
+        ps.workspace().fill_(0xFF)
+        got = [torch.full_like(t, 3.0) for t in (tq, tk, tv)]
+        for stages in order:
+            assert torch.all(got[0] == 3.0)
+            ps.bwd_stages(tq, tk, tv, out, lse, tdo, scale, *got, stages)
+        torch.cuda.synchronize()
+        assert all(torch.equal(g, w) for g, w in zip(got, want)), order
