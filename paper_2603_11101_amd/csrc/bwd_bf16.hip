@@ -290,10 +290,7 @@ __global__ __launch_bounds__(256, D <= 128 ? 2 : 1) void bwd_dkdv_kernel(AttnPar
         // this wave's 32 key rows; the lane owns key row jw + l32 (local index in the sample)
         const int jw = cur.kv_row0 - cur.seq_row0 + 32 * wave;
         const MaskBounds mask(cur.P, cur.P2, L, p.mask_mode);
-        // rows from some_from up to some_end - 1 see one of the wave's keys, rows from all_from up to all_end - 1 all of them
-        const int last_key = min(jw + 31, L - 1);
-        const int some_from = mask.first_row(jw), some_end = mask.end_row(last_key);
-        const int all_from = mask.first_row(last_key), all_end = mask.end_row(jw);
+        const KeyBlock keys(mask, jw);
 
         f32x16 dk[DT], dv[DT];
 #pragma unroll
@@ -328,9 +325,9 @@ __global__ __launch_bounds__(256, D <= 128 ? 2 : 1) void bwd_dkdv_kernel(AttnPar
             for (int qb = 0; qb < QB; ++qb) {
                 const int i0 = q0 + 32 * qb;  // first query row of the block (local index in the sample)
                 if (i0 >= L) break;
-                if (i0 + 31 < some_from || i0 >= some_end) continue;  // no pair of this block is visible
+                if (i0 + 31 < keys.some_from || i0 >= keys.some_end) continue;  // no pair of this block is visible
                 // rows past the sample read as zeros and must get p = 0: they count as seeing no key
-                const bool need_mask = i0 < all_from || i0 + 31 >= all_end;
+                const bool need_mask = i0 < keys.all_from || i0 + 31 >= keys.all_end;
 
                 // S = Q K^T and dP = dO V^T: rows = query rows (registers), columns = key rows (lanes).
                 // MFMAs alternate between the two accumulators so that none waits on the one just issued.
