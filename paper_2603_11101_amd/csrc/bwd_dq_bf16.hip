@@ -40,6 +40,11 @@ __global__ __launch_bounds__(256, D <= 128 ? 2 : 1) void bwd_dq_kernel(AttnParam
     static_assert(TILE_BYTES % FragAddr<D>::kTileAlign == 0 && (32 * D * 2) % FragAddr<D>::kTileAlign == 0,
                   "fragment addresses take tile and slice offsets in multiples of the tile alignment");
     constexpr int PF = D == 128 ? 2 : kPrefetch;  // fragment reads in flight; D = 128 has no registers to spare
+    // Tile copies that derive their offsets anew spare the registers that were spilled with up to four stacked heads at
+    // D = 128: 14 to 24 under the window, now 2 (16384-token samples, 32 / 8 heads, W = 1024, 1603 -> 1585 us; 40k tokens
+    // of heavy-tailed lengths, W = 300, 453 -> 428 and causal 825 -> 826).  Eight heads, and the head
+    // dimensions below 128 of this geometry, are faster without (16 / 2 heads, W = 300, 216 us, with 219; D = 80 170.5, with 171.5).
+    constexpr bool FRESH = DR == 128 && HPB < 8;
     extern __shared__ __attribute__((aligned(16))) char smem[];  // two stages, each a K tile then a V tile
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -51,7 +56,7 @@ __global__ __launch_bounds__(256, D <= 128 ? 2 : 1) void bwd_dq_kernel(AttnParam
     const int kv_row_bytes = p.Hkv * DR * 2;
     const int tile_step = __builtin_amdgcn_readfirstlane(BN * kv_row_bytes);
     const unsigned smem_lds = lds_addr(smem);
-    AsyncTile<D, BN, 4, DR> loader;
+    AsyncTile<D, BN, 4, DR, FRESH> loader;
     loader.init(wave, lane, kv_row_bytes);
     const FragAddr<D> fa(lane);
     const float c = p.scale * kLog2e;

@@ -241,7 +241,7 @@ VA_DEV void wait_async_loads_except() {
 // geometry of D: chunk positions from DR / 8 on are not fetched (their lanes aim past the buffer and the
 // hardware writes zeros).  Row bytes are then no multiple of the tile's row size, so the chunk can no
 // longer be XOR-ed inside the byte offset and travels in a register of its own.
-template <int D, int ROWS, int NWAVES, int DR = D>
+template <int D, int ROWS, int NWAVES, int DR = D, bool FRESH = false>
 struct AsyncTile {
     static constexpr int CPR = D / 8;
     static constexpr int RPI = 64 / CPR;
@@ -302,13 +302,15 @@ struct AsyncTile {
         }
     }
     // offset of the lane's chunk in instruction j; derived where it is used instead of keeping PER_WAVE of them in
-    // registers (the row step is made opaque, not the lane's constant: that costs no copy)
+    // registers (the row step is made opaque, not the lane's constant: that costs no copy; but the constant's exclusive-ors
+    // then stay in registers, which FRESH frees at the price of the copy)
     VA_DEV int lane_offset(int j) const {
-        int step = j * row_step;
+        int step = j * row_step, v = voff0;
         if (j > 0) asm volatile("" : "+s"(step));
-        if constexpr (DR == D) return (voff0 ^ (swizzle<D>(j * RPI) << 4)) + step;
+        if constexpr (FRESH) asm volatile("" : "+v"(v));
+        if constexpr (DR == D) return (v ^ (swizzle<D>(j * RPI) << 4)) + step;
         const int c = chunk0 ^ swizzle<D>(j * RPI);
-        return c < DR / 8 ? voff0 + step + (c << 4) : 0x7ffffff0;
+        return c < DR / 8 ? v + step + (c << 4) : 0x7ffffff0;
     }
 };
 
