@@ -298,6 +298,14 @@ int va_quantize_e4m3_per_head_device(const void* x_bf16, int32_t T, int32_t H, i
 int va_bwd_has_delta_kernel(int32_t head_dim);
 
 /*
+ * (This library's own, likewise.)  Which kernels a pass launches for the stream this list was built for:
+ *   0      those for streams that fill the chip (and always for the FP8 forward)
+ *   1..n   those that split a work over more workgroups; dK/dV: with the steps of a key row dealt to n of them
+ * VA_EINVAL for a null pointer, something that is no list, or other head counts than it was built for.  Host only.
+ */
+int va_worklist_few_works(const void* worklist_host, int32_t num_q_heads, int32_t num_kv_heads);
+
+/*
  * The backward restricted to some of its kernels (this library's own; the
  * paper names no such call).  `stages` is a non-empty combination of
  *   VA_BWD_STAGE_DELTA  delta = rowsum(dO * O) (kept negated) and LSE * log2(e) into the workspace

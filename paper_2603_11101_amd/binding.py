@@ -62,7 +62,7 @@ _lib = _load()
 
 EXPORTS = ["va_last_error", "va_pack_first_fit", "va_bin_layout", "va_tile_shape", "va_worklist_size",
            "va_build_worklist", "va_check_worklist", "va_quantize_e4m3_per_head", "va_quantize_e4m3_per_head_device",
-           "varlen_attn_bwd_workspace_bytes", "va_bwd_has_delta_kernel",
+           "varlen_attn_bwd_workspace_bytes", "va_bwd_has_delta_kernel", "va_worklist_few_works",
            "varlen_attn_fwd", "varlen_attn_bwd", "varlen_attn_bwd_stages", "varlen_attn_bwd_static", "varlen_attn_fwd_fp8",
            "va_quantize_e4m3_blockwise", "va_quantize_e4m3_blockwise_device", "varlen_attn_fwd_fp8_blockwise"]
 
@@ -264,6 +264,16 @@ def varlen_attn_bwd_workspace_bytes(shape):
 
 def va_bwd_has_delta_kernel(head_dim):
     return bool(_lib.va_bwd_has_delta_kernel(ctypes.c_int32(head_dim)))
+
+
+def va_worklist_few_works(worklist_host, num_q_heads, num_kv_heads):
+    """0 if the pass of this list runs on the kernels for streams that fill the chip, else the number of workgroups that
+    share the steps of a row on those for few works (more than 1 for dK/dV only)."""
+    wl = _i32(worklist_host)
+    if wl.size < 16 or wl.size < 8 * int(wl.reshape(-1)[14]):  # the library cannot see the array's length
+        raise ValueError(f"a work list of {wl.size} words is cut short")
+    n = _lib.va_worklist_few_works(_ptr(wl), ctypes.c_int32(num_q_heads), ctypes.c_int32(num_kv_heads))
+    return n if n >= 0 else _check(n)
 
 
 # The device calls.  The underscored forms take the host arrays as addresses: PackedStream, which keeps its arrays,

@@ -48,20 +48,31 @@ int check_shape(const va_shape* s, const int32_t* cu, const int32_t* prefix_lens
 }
 
 // Whether a pass runs on the kernels of few_util.h: a quarter of the rows and of the serial walk per workgroup.
-//   Forward, dQ: those workgroups read four times as many tiles from L2 per row, so they pay while they fit the chip
-//   in one go: 256 CUs hold one, two or three of them at head_dim 256, 128, 64.  Measured at that line (forward,
-//   kernel us, few / persistent): 64 works of D = 256 20.6 / 33.2, 128 works 62.6 / 60.0; 128 works of D = 128
-//   28.5 / 34.1, 136 ragged ones 12.9 / 10.6; 144 works of D = 64 9.4 / 9.7, 216 works 19.4 / 18.8.
+// Kernel times below are us, few / persistent, on uniform causal samples.
+//   Forward, dQ: a walk (heaviest, in tiles of 64 keys) becomes a quarter as long, for four workgroups with a prologue
+//   and a merge of their own.  Up to 64 works each has a CU to itself and gains from the second tile on (forward, 64 works
+//   of 2 tiles: D = 64 4.9 / 5.5, D = 128 6.4 / 6.8, D = 256 10.2 / 10.7; dQ 5.7 / 6.4, 8.0 / 8.8 and 13.3 / 15.9, where
+//   a delta pass is saved as well).  Streams of one tile lose (4.8 / 4.5, 6.0 / 5.5, 9.9 / 8.9; 5.6 / 5.4, 7.7 / 7.2) and
+//   stay here all the same: a short sample's bits are those it has beside longer ones.
+//   Two on a CU gain later: up to 128 works of h and h - 1 tiles, forward D = 64 6.2 / 6.7 and 6.0 / 5.9, D = 128 9.7 / 10.4
+//   and 9.3 / 9.2; dQ 7.9 / 8.2 and 7.6 / 7.1, 13.6 / 14.2 and 13.2 / 12.5, 30.7 / 32.9 and 28.8 / 28.6.  A CU holds one
+//   at D = 256: the forward never gains there (8 tiles 23.1 / 20.9).  Three on a CU at D = 64, 160 works: forward of 7 and
+//   5 tiles 7.8 / 8.4 and 7.6 / 7.2, dQ of 7 tiles 10.5 / 10.5; at D = 128 15.6 / 12.2 even for 8.
 //   dK/dV: works differ by the length of the walk over the query tiles, and the kernel of bwd_bf16.hip ends with its
-//   longest.  Here the total counts instead, at about 1 / ratio of the longest: 10.6 steps per slot, longest 54,
-//   D = 128 44 / 60 us, 24 per slot 80 / 68; D = 256, 83 per slot, longest 256, 306 / 505.  (Two steps of
-//   fixed cost per work: thousands of tiny works stay where they are.)
+//   longest.  Here the total counts instead, with ten steps of fixed cost per work, at about 1 / ratio of the longest.  On
+//   190 ragged streams at three head counts per geometry this line is within 0.4 % of the better choice on average and
+//   takes none to these kernels that they slow down.  On its two sides: D = 64 27.5 / 25.5 and 40.3 / 43.9, D = 128
+//   46.1 / 40.7 and 63.2 / 73.4, D = 256 67.6 / 64.0 and 102.4 / 113.4.
 bool few_works(int32_t pass, int32_t head_dim, int64_t works, int64_t steps, int64_t heaviest) {
     const int32_t D = tile_geometry(head_dim);
-    if (pass == VA_PASS_FWD) return works <= (D == 256 ? 64 : D == 128 ? 128 : 160);
-    if (pass == VA_PASS_BWD_DQ) return works <= 128;
-    const int64_t ratio = D == 256 ? 50 : D == 128 ? 36 : 45;
-    return 100 * (steps + kWorkFixedCost * works) < ratio * (heaviest + kWorkFixedCost) * persistent_workgroups(pass, head_dim);
+    if (pass == VA_PASS_BWD_DKDV) {
+        const int64_t ratio = D == 256 ? 56 : D == 128 ? 44 : 60;
+        return 100 * (steps + 10 * works) < ratio * heaviest * persistent_workgroups(pass, head_dim);
+    }
+    const bool fwd = pass == VA_PASS_FWD;
+    if (works <= 64) return true;
+    if (works <= 128) return D == 256 ? !fwd && heaviest >= 7 : heaviest >= (D == 128 ? 6 : 4);
+    return fwd && D == 64 && works <= 160 && heaviest >= 7;
 }
 
 // Splits of the dK/dV pass on those kernels: with few works of very many steps (one KV head serving eight query heads,
@@ -71,6 +82,21 @@ bool few_works(int32_t pass, int32_t head_dim, int64_t works, int64_t steps, int
 int32_t few_splits(int32_t head_dim, int64_t items, int64_t works, int64_t blocks, int32_t most) {
     const int64_t s = std::min<int64_t>(most / items, persistent_workgroups(VA_PASS_BWD_DKDV, head_dim) / (4 * works));
     return s > 1 && blocks * (s - 1) >= 12 * 4 * s ? (int32_t)s : 1;
+}
+
+// Inner-loop steps of a work of this item.
+int64_t item_steps(int32_t pass, const int32_t* it, int32_t mask_mode, int32_t cols, int32_t group) {
+    if (pass == VA_PASS_BWD_DKDV) return (int64_t)it[4] * group;
+    return it[5] - first_visible(it[0] - it[2], it[6] < 0 ? 0 : it[6], mask_mode) / cols;
+}
+
+// Which kernels run a list: lay->few and lay->few_splits.
+void choose_kernels(int32_t pass, int32_t head_dim, int32_t Hkv, int32_t cols, int64_t steps, int64_t heaviest,
+                    WorklistLayout* lay) {
+    lay->few = lay->num_items > 0 && lay->num_merges == 0 && few_works(pass, head_dim, lay->num_works, steps, heaviest);
+    if (pass == VA_PASS_BWD_DKDV && lay->few)
+        lay->few_splits = few_splits(head_dim, lay->num_items, lay->num_works, heaviest * cols / 32,
+                                     max_partial_slots(head_dim, Hkv));
 }
 
 // The host copy of a work list is checked against the stream it claims to
@@ -154,8 +180,7 @@ int check_worklist(const void* dev, const void* host, const va_shape* s, const i
             if (it[5] != (kv_len + cols - 1) / cols || it[4] < 0 || it[4] > visible(r0, L, Pm, P2m, s->mask_mode) / cols)
                 return fail(VA_EINVAL, "%s: work item %d has a bad key range", who, i);
         }
-        const int64_t work = pass == VA_PASS_BWD_DKDV ? (int64_t)it[4] * (s->num_q_heads / s->num_kv_heads)
-                                                      : it[5] - first_visible(row0 - seq0, Pm, s->mask_mode) / cols;
+        const int64_t work = item_steps(pass, it, s->mask_mode, cols, s->num_q_heads / s->num_kv_heads);
         steps += work * lay.works_per_item;
         heaviest = std::max(heaviest, work);
     }
@@ -215,9 +240,7 @@ int check_worklist(const void* dev, const void* host, const va_shape* s, const i
     if (at != lay.num_works) return fail(VA_EINVAL, "%s: workgroup table does not partition the works", who);
     *layout = lay;
     layout->flags = h1[3];
-    layout->few = few_works(pass, s->head_dim, lay.num_works, steps, heaviest) && num_merges == 0;
-    if (pass == VA_PASS_BWD_DKDV && layout->few && n > 0)
-        layout->few_splits = few_splits(s->head_dim, n, lay.num_works, heaviest * cols / 32, max_slots);
+    choose_kernels(pass, s->head_dim, s->num_kv_heads, cols, steps, heaviest, layout);
     return VA_OK;
 }
 
@@ -403,6 +426,29 @@ int varlen_attn_bwd(const void* q, const void* k, const void* v, const void* out
     return varlen_attn_bwd_stages(q, k, v, out, lse, dout, cu_seqlens, prefix_lens, worklist_dkdv, worklist_dkdv_host,
                                   worklist_dq, worklist_dq_host, shape, scale, dq, dk, dv, workspace, workspace_bytes,
                                   stream, VA_BWD_STAGE_ALL);
+}
+
+int va_worklist_few_works(const void* host, int32_t num_q_heads, int32_t num_kv_heads) {
+    const char* who = "va_worklist_few_works";
+    if (!host) return fail(VA_EINVAL, "%s: null work list", who);
+    const WorkItem* w = static_cast<const WorkItem*>(host);
+    const int32_t *h = w[0].w, *h1 = w[1].w;
+    const int32_t pass = h[1], D = h[4], n = h[6];
+    int32_t rows, cols;
+    if (h[0] != kWorklistMagic) return fail(VA_EINVAL, "%s: not a work list", who);
+    const int rc = tile_shape(pass, D, num_q_heads, num_kv_heads, &rows, &cols);
+    if (rc) return rc;
+    WorklistLayout lay = worklist_layout(pass, D, num_q_heads, num_kv_heads, n, h1[7]);
+    if (n < 0 || h1[7] < 0 || h[2] != rows || h1[2] != lay.works_per_item || h1[6] != lay.total_recs)
+        return fail(VA_EINVAL, "%s: the list was built for other head counts", who);
+    int64_t steps = 0, heaviest = 0;
+    for (int32_t i = 0; i < n; ++i) {
+        const int64_t work = item_steps(pass, w[lay.item_rec + i].w, h[5], cols, num_q_heads / num_kv_heads);
+        steps += work * lay.works_per_item;
+        heaviest = std::max(heaviest, work);
+    }
+    choose_kernels(pass, D, num_kv_heads, cols, steps, heaviest, &lay);
+    return lay.few ? lay.few_splits : 0;
 }
 
 int va_bwd_has_delta_kernel(int32_t head_dim) { return dq_computes_delta(head_dim) ? 0 : 1; }

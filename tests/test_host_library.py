@@ -694,3 +694,47 @@ def test_a_plan_saved_without_addresses_still_runs():
         with pytest.raises(va.VarlenAttnError) as e:  # cu_seqlens has been read; the tensors come next
             call()
         assert e.value.code in (va.VA_EALIGN, va.VA_EHIP)  # bwd_static asks for its scratch memory first
+
+
+def _few(lens, Hq, Hkv, D, mode=va.VA_MASK_CAUSAL, ends=None):
+    """For forward, dQ and dK/dV of a stream: workgroups that share a row's steps on the kernels for few works, or 0."""
+    cu = np.concatenate([[0], np.cumsum(lens)])
+    return [va.va_worklist_few_works(va.va_build_worklist(cu, ends, mode, p, D, Hq, Hkv), Hq, Hkv)
+            for p in (va.VA_PASS_FWD, va.VA_PASS_BWD_DQ, va.VA_PASS_BWD_DKDV)]
+
+
+@pytest.mark.parametrize("lens,heads,few", [
+    ([59] * 32, (2, 2, 64), (1, 1)), ([123] * 32, (2, 2, 64), (1, 1)), ([187] * 24, (2, 2, 64), (0, 0)),
+    ([251] * 24, (2, 2, 64), (1, 1)), ([379] * 26, (2, 2, 64), (0, 0)), ([443] * 20, (2, 2, 64), (1, 0)),
+    ([123] * 16, (4, 4, 128), (1, 1)), ([128] * 24, (4, 4, 128), (0, 0)), ([315] * 10, (4, 4, 128), (0, 0)),
+    ([379] * 10, (4, 4, 128), (1, 1)), ([507] * 10, (4, 4, 128), (0, 0)),
+    ([59] * 17, (4, 4, 256), (0, 0)), ([128] * 16, (8, 1, 256), (0, 0)), ([379] * 4, (8, 1, 256), (0, 0)),
+    ([443] * 4, (8, 1, 256), (0, 1)), ([64], (1, 1, 64), (1, 1)), ([], (1, 1, 64), (0, 0)), ([0, 0], (8, 1, 256), (0, 0))])
+def test_forward_and_dq_of_few_works_need_walks_long_enough(lens, heads, few):
+    """Up to 64 works whatever the lengths; from there on the side that measured faster."""
+    assert tuple(_few(lens, *heads)[:2]) == few
+
+
+@pytest.mark.parametrize("heads,n,top,few", [
+    ((4, 4, 64), 28, 400, 0), ((4, 4, 64), 14, 1100, 1), ((4, 4, 128), 28, 400, 0), ((4, 4, 128), 23, 1100, 0),
+    ((8, 4, 128), 20, 1100, 1), ((4, 4, 256), 21, 400, 0), ((8, 4, 256), 11, 1100, 1), ((8, 1, 256), 90, 400, 1)])
+def test_dkdv_of_few_works_weighs_the_total_against_the_longest(heads, n, top, few):
+    """On the side that measured faster: works cost something whatever their length, short ones relatively more."""
+    lens = np.random.default_rng(n // 8).integers(60, top, size=n)
+    assert _few(lens, *heads)[2] == few
+
+
+def test_the_kernels_of_a_list_are_asked_with_the_head_counts_it_was_built_for():
+    wl = va.va_build_worklist([0, 300], None, va.VA_MASK_CAUSAL, va.VA_PASS_FWD, 128, 4, 2)
+    assert va.va_worklist_few_works(wl, 4, 2) == 1
+    # a window of one tile shortens the walk
+    assert _few([700] * 2, 4, 4, 128)[0] == 1 and _few([700] * 2, 4, 4, 128, va.VA_MASK_SLIDING_WINDOW, [64, 64])[0] == 1
+    assert _few([700] * 5, 4, 4, 128)[0] == 1 and _few([700] * 5, 4, 4, 128, va.VA_MASK_SLIDING_WINDOW, [64] * 5)[0] == 0
+    for hq, hkv in ((8, 2), (2, 2), (4, 4)):
+        with pytest.raises(va.VarlenAttnError) as e:
+            va.va_worklist_few_works(wl, hq, hkv)
+        assert e.value.code == va.VA_EINVAL
+    with pytest.raises(va.VarlenAttnError):
+        va.va_worklist_few_works(np.zeros_like(wl), 4, 2)
+    with pytest.raises(ValueError):
+        va.va_worklist_few_works(wl[:-1], 4, 2)
