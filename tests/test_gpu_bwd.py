@@ -151,8 +151,9 @@ def test_random_configurations_forward_and_backward(trial):
 @pytest.mark.parametrize("D", [48, 64, 80, 96, 128, 160, 192, 256])
 @pytest.mark.parametrize("G", [1, 2, 4, 8])
 def test_every_head_dimension_with_every_head_stacking(D, G):
-    # The forward and dQ kernels are instantiated per (head dimension, query heads stacked in a block of rows:
-    # 1, 2, 4 or 8 = the group size here): each of the 32 once, forward and backward, the mask cycling with the case.
+    # Every head dimension with every number of query heads stacked in a block of rows (1, 2, 4 or 8 = the group size
+    # here), forward and backward, the mask cycling with the case.  Streams this small run on the kernels for few works;
+    # test_gpu_both_sides.py runs the persistent ones, which are instantiated per pair.
     Hkv = 2 if G <= 2 else 1
     mode = list(MODES)[(D // 16 + G) % len(MODES)]
     lens = [70, 0, 129, 33, 200]
