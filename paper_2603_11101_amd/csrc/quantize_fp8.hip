@@ -129,8 +129,9 @@ VA_DEV unsigned* partial_word(unsigned char* codes, int r, int k, int H, int D, 
     return reinterpret_cast<unsigned*>(codes + (row * H + h0) * D) + k % words_per_row;
 }
 
-// Bound by the read.  A run is every R-th row, so that the workgroups sweep the tensor side by side: with runs of
-// consecutive rows, which start at like addresses, the 67 MB of 16384 tokens x 16 heads x 128 took 20.7 us instead
+// Mostly the read: the 67 MB of 16384 tokens x 16 heads x 128 take 14.1 us in a train of calls, 2.0 of them the maxima, which
+// go a word at a time to every run (17.9 us behind other kernels).  A run is every R-th row, so that the workgroups
+// sweep the tensor side by side: with runs of consecutive rows, which start at like addresses, it was 20.7 us instead
 // of 17.9, and more loads in flight per thread made it worse (8 instead of 2: 24.8).
 __global__ __launch_bounds__(kQuantThreads) void quant_partial_max_kernel(const u32x4* x, int T, int H, int D, int runs,
                                                                          unsigned char* codes) {
