@@ -11,7 +11,7 @@ from oracle import attn as oa
 from paper_2603_11101_amd import binding as va
 from paper_2603_11101_amd import workloads as wl
 
-from gpu_util import DEV, TOL_FWD_REL, TOL_GRAD_REL, TOL_LSE_ABS, from_dev_bf16, max_abs, rel_l2, to_dev_bf16
+from gpu_util import DEV, DeviceRun, TOL_FWD_REL, TOL_GRAD_REL, TOL_LSE_ABS, from_dev_bf16, max_abs, rel_l2, to_dev_bf16
 
 pytestmark = pytest.mark.gpu
 
@@ -171,3 +171,25 @@ def test_backward_by_stages_on_the_persistent_kernels(Hq, Hkv, D):
     first = va.VA_BWD_STAGE_DQ | (va.VA_BWD_STAGE_DELTA if va.va_bwd_has_delta_kernel(D) else 0)
     parts = c.run(stages=(first, va.VA_BWD_STAGE_DKDV))
     assert all(same_bits(whole[n], parts[n]) for n in NAMES)
+
+
+@pytest.mark.parametrize("Hq,Hkv,D,splits", [(4, 4, 128, (1, 1)), (8, 1, 256, (16, 8))])
+def test_bits_of_a_sample_beside_another_on_the_kernels_for_few_works(Hq, Hkv, D, splits):
+    # O, LSE and dQ have the bits of the sample alone; dK and dV as long as their steps are dealt to as many workgroups
+    L = 430
+    cu, _, q, k, v, do = wl.random_stream(8800 + D, [L, L], Hq, Hkv, D)
+    scale = 1.0 / np.sqrt(D)
+    print(f"beside another D={D} heads={Hq}/{Hkv}", flush=True)
+    runs = []
+    for n in (1, 2):
+        run = DeviceRun(cu[:n + 1], None, va.VA_MASK_CAUSAL, *(x[:n * L] for x in (q, k, v, do)), scale)
+        few = [va.va_worklist_few_works(run.ps.worklist_host[p], Hq, Hkv) for p in PASSES]
+        assert few == [1, splits[n - 1], 1]
+        runs.append(run)
+    alone, beside = runs
+    assert np.array_equal(beside.out[:L], alone.out) and np.array_equal(beside.lse[:, :L], alone.lse)
+    assert np.array_equal(beside.dq[:L], alone.dq)
+    for n in ("dk", "dv"):
+        a, b = getattr(alone, n), getattr(beside, n)[:L]
+        # the sums differ in order alone: float32 rounding, then at most a last place of bfloat16 where that falls on an edge
+        assert np.array_equal(a, b) if splits[0] == splits[1] else rel_l2(b, a) <= 2.0 ** -8, n
