@@ -118,7 +118,8 @@ class Case:
                  "dq": torch.empty_like(q), "dk": torch.empty_like(k), "dv": torch.empty_like(v)}
             self.sets.append(s)
         self.ps.workspace()
-        self.fused = not va.va_bwd_has_delta_kernel(D)
+        self.fused = (not va.va_bwd_has_delta_kernel(D)
+                      or va.va_worklist_few_works(self.ps.worklist_host[va.VA_PASS_BWD_DQ], Hq, Hkv) > 0)
 
     # -- launches
     def fwd(self, i=0):

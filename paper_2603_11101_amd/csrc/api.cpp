@@ -438,8 +438,12 @@ int va_worklist_few_works(const void* host, int32_t num_q_heads, int32_t num_kv_
     if (h[0] != kWorklistMagic) return fail(VA_EINVAL, "%s: not a work list", who);
     const int rc = tile_shape(pass, D, num_q_heads, num_kv_heads, &rows, &cols);
     if (rc) return rc;
+    // (before any product with the number of items: the words of something that is no list may be anything)
+    const int64_t works = (int64_t)n * works_per_item(pass, num_q_heads, num_kv_heads);
+    if (n < 0 || works > INT32_MAX / 2 || works != h1[1] || h1[7] < 0 || h1[7] > kMaxPartialSlots)
+        return fail(VA_EINVAL, "%s: the list was built for other head counts", who);
     WorklistLayout lay = worklist_layout(pass, D, num_q_heads, num_kv_heads, n, h1[7]);
-    if (n < 0 || h1[7] < 0 || h[2] != rows || h1[2] != lay.works_per_item || h1[6] != lay.total_recs)
+    if (h[2] != rows || h1[2] != lay.works_per_item || h1[6] != lay.total_recs)
         return fail(VA_EINVAL, "%s: the list was built for other head counts", who);
     int64_t steps = 0, heaviest = 0;
     for (int32_t i = 0; i < n; ++i) {

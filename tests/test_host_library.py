@@ -736,5 +736,10 @@ def test_the_kernels_of_a_list_are_asked_with_the_head_counts_it_was_built_for()
         assert e.value.code == va.VA_EINVAL
     with pytest.raises(va.VarlenAttnError):
         va.va_worklist_few_works(np.zeros_like(wl), 4, 2)
+    for word, value in (((0, 6), 2 ** 30), ((0, 6), -1), ((0, 6), 2), ((1, 1), 2 ** 30), ((1, 7), 10 ** 9), ((0, 1), 7), ((0, 4), 72)):
+        bad = wl.copy()
+        bad[word] = value
+        with pytest.raises(va.VarlenAttnError):
+            va.va_worklist_few_works(bad, 4, 2)
     with pytest.raises(ValueError):
         va.va_worklist_few_works(wl[:-1], 4, 2)
